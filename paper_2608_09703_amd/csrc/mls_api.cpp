@@ -92,7 +92,8 @@ struct Plan {
   int M = 0;
   int s = 0;
   bool f32 = false;
-  bool wide = false;  // wide bf16 tile core (every width a multiple of 64)
+  bool wide = false;   // wide bf16 tile core
+  bool ktail = false;  // some width is not a multiple of the wide core's 64-wide K-tile
   int es = 2;
   int64_t T = 0, V = 0;
   int64_t sumd = 0;
@@ -174,7 +175,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
   pl.sumd = 0;
   for (int i = 0; i < p->M; ++i) pl.sumd += p->d[i];
   pl.wide = !pl.f32;
-  for (int i = 0; i < p->M; ++i) pl.wide = pl.wide && (p->d[i] % 64 == 0);
+  for (int i = 0; i < p->M; ++i) pl.ktail = pl.ktail || p->d[i] % 64 != 0;
   pl.T_pad = round_up(p->T, kFusedBN);
   pl.n_tt = (int)(pl.T_pad / kFusedBN);
   const int fbm = fused_tile_rows(pl.wide);
@@ -191,7 +192,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
     // would exceed kSlabTargetBytes (the wide path keeps one slab layout, the
     // general path two), so the logit-gradient slab never spans the whole
     // vocabulary (V > 256).
-    const int64_t per_row = (pl.wide_bwd ? 1ll : 2ll) * pl.M * pl.T_pad * pl.es;
+    const int64_t per_row = (pl.wide_bwd && !pl.ktail ? 1ll : 2ll) * pl.M * pl.T_pad * pl.es;
     const int64_t fit = std::max<int64_t>(256, kSlabTargetBytes / per_row / 256 * 256);
     const int64_t n = std::max<int64_t>(kMinChunks, (p->V + fit - 1) / fit);
     vc = round_up((p->V + n - 1) / n, 256);
@@ -199,7 +200,12 @@ void make_plan(const mls_problem* p, Plan& pl) {
   if (pl.wide_bwd) {
     // one slab [T_pad][Vc] and one head chunk [Vc][d_i] below 4 GiB each
     const int64_t cap = std::min(kPanelMax / (pl.T_pad * pl.es), kPanelMax / (dmax * pl.es)) / 256 * 256;
-    vc = std::min(vc, cap);
+    // widths that are not multiples of 64 keep the chunk width they were given:
+    // a wider one goes to the general kernels
+    if (!pl.ktail)
+      vc = std::min(vc, cap);
+    else if (std::min(vc, vmax) > cap)
+      pl.wide_bwd = false;
   }
   pl.Vc = std::max<int64_t>(256, std::min(vc, vmax));
   pl.n_chunks = (int)((p->V + pl.Vc - 1) / pl.Vc);
@@ -265,7 +271,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
   // [V, d_i] must also fit one wide-GEMM operand
   pl.fb_ld = (int64_t)pl.n_vt_fwd * kFusedBN;
   const bool heads_fit = pl.V * dmax * pl.es <= kPanelMax;
-  pl.fb_store = pl.wide && p->T > kFusedBN && heads_fit && !(p->flags & MLS_FWD_BWD_RECOMPUTE);
+  pl.fb_store = pl.wide && !pl.ktail && p->T > kFusedBN && heads_fit && !(p->flags & MLS_FWD_BWD_RECOMPUTE);
   if (pl.fb_store) {
     const int64_t row = pl.fb_ld * 2;
     int64_t cap = std::min<int64_t>(kPanelMax / row, kLogitSlabBudget / (row * pl.M));
@@ -320,6 +326,7 @@ void fill_common(const mls_problem* p, const Plan& pl, FusedArgs& a) {
   a.tau = p->tau;
   a.inv_tau = 1.0f / p->tau;
   a.wide = pl.wide ? 1 : 0;
+  a.ktail = pl.ktail ? 1 : 0;
   // vocabulary tiles per group of the tile order: measured best at 8 for
   // T <= 4096 and at 4 from T = 8192 on (V = 128,256 and 262,144 shapes)
   a.group_v = pl.n_tt >= 64 ? 4 : 8;
@@ -986,6 +993,7 @@ mls_status mls_diagnostics(const mls_problem* p, float* kl_pair, float* agree, i
   a.ignore_index = p->ignore_index;
   a.n_tt = pl.n_tt_diag;
   a.n_vt = pl.n_vt_diag;
+  a.ktail = pl.ktail ? 1 : 0;
   a.group_v = 4;  // measured: 4 > 8 > 16 here (8 for the forward and backward)
   a.partials = reinterpret_cast<float*>(ws + pl.off_dpart);
   a.rowvals = reinterpret_cast<float*>(ws + pl.off_drow);
@@ -997,7 +1005,7 @@ mls_status mls_diagnostics(const mls_problem* p, float* kl_pair, float* agree, i
   hipError_t e;
   {
     ProfScope ps("diag_tiles", s);
-    e = launch_diag_tiles(a, pl.f32, pl.wide, s);
+    e = launch_diag_tiles(a, pl.f32, s);
   }
   if (e != hipSuccess) return hip_fail(e, "diagnostics tile launch");
   {
@@ -1181,9 +1189,9 @@ mls_status mls_head_logits(int64_t T, int64_t V, int64_t d, int32_t dtype, const
   a.o = o;
   a.W = W;
   a.logits = logits;
-  const bool wide = dtype == MLS_BF16 && d % 64 == 0;
+  const bool wide = dtype == MLS_BF16;
   a.n_tt = (int)((T + head_tile() - 1) / head_tile());
-  const int rows = wide ? head_tile_rows(true, a.n_tt) : 128;
+  const int rows = head_tile_rows(wide, a.n_tt);
   a.n_vt = (int)((V + rows - 1) / rows);
   // tile order (groups of vocabulary tiles), measured on the verifier's 714
   // rows with 192-row tiles: groups of 2 or 4 0.731-0.742 ms per decode step,
@@ -1193,7 +1201,7 @@ mls_status mls_head_logits(int64_t T, int64_t V, int64_t d, int32_t dtype, const
   hipError_t e;
   {
     ProfScope ps("head_logits", st);
-    e = launch_head_logits(a, dtype == MLS_F32, wide, rows, st);
+    e = launch_head_logits(a, dtype == MLS_F32, rows, st);
   }
   if (e != hipSuccess) return hip_fail(e, "head logits launch");
   return MLS_OK;

@@ -13,9 +13,10 @@
 //  - STAGES K-tiles of RB bytes (64 or 32 bf16) are in flight; a K-tile is consumed after an
 //    explicit vmcnt wait and a plain s_barrier (no memory fence, so younger
 //    loads stay in flight across the barrier);
-//  - K must be a multiple of 64 (RB = 128) or 32 (RB = 64) and the operand
-//    row stride at least K; a
-//    panel must be below 4 GiB.
+//  - K of an MC operand is a multiple of a K-tile; K of KC operands too unless
+//    KTAIL is set, which takes any multiple of 8: the last K-tile's lanes past
+//    the row end get an offset outside the panel and read zero. The operand
+//    row stride is at least K, a panel below 4 GiB (2 GiB with KTAIL).
 #pragma once
 
 #include "mls_device.h"
@@ -142,7 +143,7 @@ __device__ __forceinline__ uint2 lds_read_tr8(const char* p) {
 // has half a K-tile of lead. It pays where a K-tile lasts long (the 256 x 256
 // GEMM tile), and costs where it does not (the 128 x 128 fused tiles).
 template <int BM, int BN, int WGM, int WGN, int STAGES, int RB = 128, int ALAY = kLayoutKC,
-          int BLAY = kLayoutKC, bool SPREAD = false>
+          int BLAY = kLayoutKC, bool SPREAD = false, bool KTAIL = false>
 struct WideMma {
   static constexpr int kBM = BM;
   static constexpr int kBN = BN;
@@ -166,6 +167,8 @@ struct WideMma {
   static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile must split evenly over the waves");
   static_assert(STAGES >= 2 && STAGES <= 4, "2..4 stages");
   static_assert(kLoadsPerTile * (STAGES - 1) < 64, "vmcnt range");
+  static_assert(!KTAIL || (RB == 128 && !SPREAD && ALAY == kLayoutKC && BLAY == kLayoutKC),
+                "K tails: K-contiguous operands, loads in one burst");
 
   f32x16_t acc[FM][FN];
 
@@ -239,6 +242,25 @@ struct WideMma {
     for (int j = 0; j < L; ++j) {
       char* dst = lds + (j * NW + wave) * 64 * 16;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)dst, 16, off[j] + vofs, sofs, 0,
+                                               0);
+    }
+  }
+
+  // As issue_operand for the K-tile at byte `sofs` of a KC operand whose rows
+  // hold `kbytes` bytes of K: chunks past them read as zero (their offset is
+  // moved outside the panel, which the descriptor's range check turns into 0).
+  template <int L>
+  __device__ __forceinline__ static void issue_operand_tail(__amdgpu_buffer_rsrc_t rsrc,
+                                                            const uint32_t* off, int sofs,
+                                                            int kbytes, char* lds, int wave,
+                                                            int lane) {
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const int slot = (j * NW + wave) * 64 + lane;
+      const int cb = swz_chunk<RB>(slot / CPR, slot % CPR) << 4;  // byte of the chunk in its K-tile
+      char* dst = lds + (j * NW + wave) * 64 * 16;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)dst, 16,
+                                               sofs + cb < kbytes ? off[j] : 0x80000000u, sofs, 0,
                                                0);
     }
   }
@@ -359,7 +381,7 @@ struct WideMma {
     const int wm = wave % WGM;
     const int wn = wave / WGM;
     init();
-    const int nk = (int)(kbytes / RB);
+    const int nk = KTAIL ? (int)((kbytes + RB - 1) / RB) : (int)(kbytes / RB);
     // KC operands: panel of BM (BN) rows, K position as scalar byte offset.
     // MC operands: panel of BM (BN) columns, K position as scalar row offset.
     const __amdgpu_buffer_rsrc_t ra = ALAY == kLayoutKC
@@ -386,6 +408,11 @@ struct WideMma {
       if (s < nk) {
         char* st = smem + s * kStageBytes;
         const uint32_t ka = s * stepa, kb = s * stepb;
+        if (KTAIL && (s + 1) * RB > kbytes) {
+          issue_operand_tail<LA>(ra, offa, (int)ka, (int)kbytes, st, wave, lane);
+          issue_operand_tail<LB>(rb, offb, (int)kb, (int)kbytes, st + BM * RB, wave, lane);
+          continue;
+        }
         issue_operand<LA>(ra, offa, ALAY == kLayoutKC ? 0u : ka, ALAY == kLayoutKC ? (int)ka : 0, st,
                           wave);
         issue_operand<LB>(rb, offb, BLAY == kLayoutKC ? 0u : kb, BLAY == kLayoutKC ? (int)kb : 0,
@@ -411,10 +438,15 @@ struct WideMma {
         if (nt < nk) {
           char* st = smem + (nt % STAGES) * kStageBytes;
           const uint32_t ka = nt * stepa, kb = nt * stepb;
-          issue_operand<LA>(ra, offa, ALAY == kLayoutKC ? 0u : ka, ALAY == kLayoutKC ? (int)ka : 0,
-                            st, wave);
-          issue_operand<LB>(rb, offb, BLAY == kLayoutKC ? 0u : kb, BLAY == kLayoutKC ? (int)kb : 0,
-                            st + BM * RB, wave);
+          if (KTAIL && (nt + 1) * RB > kbytes) {
+            issue_operand_tail<LA>(ra, offa, (int)ka, (int)kbytes, st, wave, lane);
+            issue_operand_tail<LB>(rb, offb, (int)kb, (int)kbytes, st + BM * RB, wave, lane);
+          } else {
+            issue_operand<LA>(ra, offa, ALAY == kLayoutKC ? 0u : ka, ALAY == kLayoutKC ? (int)ka : 0,
+                              st, wave);
+            issue_operand<LB>(rb, offb, BLAY == kLayoutKC ? 0u : kb, BLAY == kLayoutKC ? (int)kb : 0,
+                              st + BM * RB, wave);
+          }
         }
         compute_stage(stage, stage + BM * RB, lane, wm, wn, [](int) {});
       } else {

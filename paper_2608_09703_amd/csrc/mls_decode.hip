@@ -1133,7 +1133,9 @@ __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
 using HeadWide = WideMma<128, 128, 2, 2, 2>;
 // 192 vocabulary rows: 80 KB of stages, two blocks fill a CU's LDS
 using HeadWide192 = WideMma<192, 128, 2, 2, 2>;
-using HeadGenBf16 = TileMma<Bf16, 128, 128, 2, 2>;
+// widths that are not multiples of the 64-wide K-tile
+using HeadWideTail = WideMma<128, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
+using HeadWide192Tail = WideMma<192, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
 using HeadGenF32 = TileMma<F32, 128, 128, 2, 2>;
 
 }  // namespace
@@ -1150,21 +1152,21 @@ int row_elems_per_thread(int64_t V) {
   return 0;
 }
 
-hipError_t launch_head_logits(const HeadArgs& a, bool f32, bool wide, int rows,
-                              hipStream_t stream) {
-  const dim3 grid((unsigned)a.n_tt * (unsigned)a.n_vt);
-  if (rows != (f32 || !wide ? 128 : head_tile_rows(wide, a.n_tt))) return hipErrorInvalidValue;
+template <class Mma, typename E>
+static void launch_head_t(const HeadArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((head_logits_kernel<Mma, E>), dim3((unsigned)a.n_tt * (unsigned)a.n_vt),
+                     dim3(Mma::NT), 0, stream, a);
+}
+
+hipError_t launch_head_logits(const HeadArgs& a, bool f32, int rows, hipStream_t stream) {
+  if (rows != head_tile_rows(!f32, a.n_tt)) return hipErrorInvalidValue;
+  const bool tail = a.d % 64 != 0;
   if (f32)
-    hipLaunchKernelGGL((head_logits_kernel<HeadGenF32, F32>), grid, dim3(HeadGenF32::NT), 0, stream,
-                       a);
-  else if (wide && rows == 192)
-    hipLaunchKernelGGL((head_logits_kernel<HeadWide192, Bf16>), grid, dim3(HeadWide192::NT), 0,
-                       stream, a);
-  else if (wide)
-    hipLaunchKernelGGL((head_logits_kernel<HeadWide, Bf16>), grid, dim3(HeadWide::NT), 0, stream, a);
+    launch_head_t<HeadGenF32, F32>(a, stream);
+  else if (rows == 192)
+    tail ? launch_head_t<HeadWide192Tail, Bf16>(a, stream) : launch_head_t<HeadWide192, Bf16>(a, stream);
   else
-    hipLaunchKernelGGL((head_logits_kernel<HeadGenBf16, Bf16>), grid, dim3(HeadGenBf16::NT), 0,
-                       stream, a);
+    tail ? launch_head_t<HeadWideTail, Bf16>(a, stream) : launch_head_t<HeadWide, Bf16>(a, stream);
   return hipGetLastError();
 }
 

@@ -19,6 +19,8 @@
 // No [T, V] tensor is formed and no forward statistics are needed.
 #include <math.h>
 
+#include <type_traits>
+
 #include "mls_core.h"
 #include "mls_device.h"
 #include "mls_launch.h"
@@ -299,29 +301,31 @@ __global__ __launch_bounds__(kRedThreads) void diag_mean_kernel(DiagArgs a) {
 // per CU; for M = 4 that no longer fits, and four waves of 64x32 (32 per
 // model) take a 128x64 tile, still two blocks per CU (two independent blocks
 // hide each other's barriers better than one eight-wave block on 128x128).
-// The general path uses the four-wave register-staged core on 128x64.
+// The fp32 path uses the four-wave register-staged core on 128x64.
 using DiagWide = WideMma<kFusedWideBM, kDiagBN, 2, 2, 2>;
 using DiagWide4 = WideMma<kFusedWideBM, kDiagBN / 2, 2, 2, 2>;
+using DiagWideTail =
+    WideMma<kFusedWideBM, kDiagBN, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
+using DiagWide4Tail =
+    WideMma<kFusedWideBM, kDiagBN / 2, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
 template <typename E>
 using DiagGen = TileMma<E, kFusedBM, kDiagGenBN, 2, 2>;
 
 template <int MM>
-hipError_t launch_tiles_m(const DiagArgs& a, bool f32, bool wide, hipStream_t stream) {
+hipError_t launch_tiles_m(const DiagArgs& a, bool f32, hipStream_t stream) {
   const dim3 grid((unsigned)a.n_tt * (unsigned)a.n_vt);
   if (f32)
     hipLaunchKernelGGL((diag_tile_kernel<DiagGen<F32>, F32, MM, 2>), grid, dim3(kThreads), 0,
                        stream, a);
-  else if (wide) {
-    if constexpr (MM <= 3)
-      hipLaunchKernelGGL((diag_tile_kernel<DiagWide, Bf16, MM, 2>), grid, dim3(DiagWide::NT), 0,
-                         stream, a);
+  else {
+    // bf16: the wide core, in its K-tail form when a width is not a multiple of 64
+    using Full = std::conditional_t<(MM <= 3), DiagWide, DiagWide4>;
+    using Tail = std::conditional_t<(MM <= 3), DiagWideTail, DiagWide4Tail>;
+    if (a.ktail)
+      hipLaunchKernelGGL((diag_tile_kernel<Tail, Bf16, MM, 2>), grid, dim3(Tail::NT), 0, stream, a);
     else
-      hipLaunchKernelGGL((diag_tile_kernel<DiagWide4, Bf16, MM, 2>), grid, dim3(DiagWide4::NT), 0,
-                         stream, a);
+      hipLaunchKernelGGL((diag_tile_kernel<Full, Bf16, MM, 2>), grid, dim3(Full::NT), 0, stream, a);
   }
-  else
-    hipLaunchKernelGGL((diag_tile_kernel<DiagGen<Bf16>, Bf16, MM, 2>), grid, dim3(kThreads), 0,
-                       stream, a);
   return hipGetLastError();
 }
 
@@ -361,12 +365,12 @@ int diag_tile_rows(bool wide) { return wide ? kFusedWideBM : kFusedBM; }
 int diag_tile_cols(bool wide, int M) { return wide ? (M == 4 ? kDiagBN / 2 : kDiagBN) : kDiagGenBN; }
 int diag_record_floats(int M) { return M * M + 3 * M; }
 
-hipError_t launch_diag_tiles(const DiagArgs& a, bool f32, bool wide, hipStream_t stream) {
+hipError_t launch_diag_tiles(const DiagArgs& a, bool f32, hipStream_t stream) {
   switch (a.M) {
-    case 1: return launch_tiles_m<1>(a, f32, wide, stream);
-    case 2: return launch_tiles_m<2>(a, f32, wide, stream);
-    case 3: return launch_tiles_m<3>(a, f32, wide, stream);
-    case 4: return launch_tiles_m<4>(a, f32, wide, stream);
+    case 1: return launch_tiles_m<1>(a, f32, stream);
+    case 2: return launch_tiles_m<2>(a, f32, stream);
+    case 3: return launch_tiles_m<3>(a, f32, stream);
+    case 4: return launch_tiles_m<4>(a, f32, stream);
   }
   return hipErrorInvalidValue;
 }

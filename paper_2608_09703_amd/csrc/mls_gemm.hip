@@ -80,9 +80,10 @@ using WideGemmW = WideMma<kWideBM, kWideBN, 2, 4, 2, 128, kLayoutMC, kLayoutMC, 
 // descriptors over the tile's existing rows (rows past them read as 0 and are
 // not written). Element (row, col) of the tile is at byte offset
 // (row * ldc + col) * size; coff[fn] is the lane's part for column block fn,
-// (its first row) * ldc + its column. A wave's 32-column block lies wholly
-// inside or outside the output (widths are multiples of 64), so blocks past it
-// are skipped by a uniform branch (ok[fn]). INSIDE (all of the tile's rows
+// (its first row) * ldc + its column, or kNoCol for a column past the output
+// (widths are multiples of 8), which the descriptor's range check then drops.
+// 32-column blocks wholly past the output are skipped by a uniform branch
+// (ok[fn]). INSIDE (all of the tile's rows
 // exist): the (fm, r) part of the row goes into the scalar offset; otherwise
 // every element gets its own vector offset, which the descriptor checks. Each
 // kind of load is one loop with no branch inside, so a wave's loads are all in
@@ -94,6 +95,9 @@ using WideGemmW = WideMma<kWideBM, kWideBN, 2, 4, 2, 128, kLayoutMC, kLayoutMC, 
 // together with the forward's non-temporal slab stores); the reads took the
 // GEMMs from 4.43-4.45 to 4.41-4.42 ms per step.
 constexpr int kStoreNT = 2;
+// In bytes (x 2 or x 4) kNoCol and any row offset added to it (256 rows of at
+// most 2^20 columns) lie past a tile's rows (at most 2^30 bytes) and below 2^32.
+constexpr uint32_t kNoCol = 0x20000000u;
 
 template <class Mma, bool INSIDE>
 struct TileIo {
@@ -237,7 +241,7 @@ __device__ __forceinline__ void wide_tile(const GemmGroup& g, int tm, int tn, in
 #pragma unroll
   for (int fn = 0; fn < FN; ++fn) {
     const int col = (int)n0 + Mma::col_of(wn, fn, lane);
-    coff[fn] = (uint32_t)(Mma::row_of(wm, 0, 0, lane) * ldc + col);
+    coff[fn] = col < next ? (uint32_t)(Mma::row_of(wm, 0, 0, lane) * ldc + col) : kNoCol;
     ok[fn] = n0 + wnu * Mma::WTN + fn * 32 < next;  // the whole 32-column block (wave-uniform)
   }
   const bool inside = m0 + Mma::kBM <= mext;

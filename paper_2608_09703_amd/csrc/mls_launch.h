@@ -13,7 +13,7 @@ constexpr int kMaxModels = 8;
 
 // Tile of the fused logits kernels: BM vocabulary rows x BN token columns.
 constexpr int kFusedBM = 128;      // general core
-constexpr int kFusedWideBM = 128;  // wide bf16 core (all widths multiples of 64)
+constexpr int kFusedWideBM = 128;  // wide bf16 core
 // forward partial records per (vocabulary tile, token, sub-model): one per
 // wave row of the tile, each over its own half of the tile's rows
 constexpr int kFusedFwdParts = 2;
@@ -45,6 +45,7 @@ struct FusedArgs {
   float tau;
   float inv_tau;
   int32_t wide;  // 1: wide bf16 core (BM = kFusedWideBM)
+  int32_t ktail;  // wide core: some width is not a multiple of its 64-wide K-tile
   int32_t group_v;  // vocabulary tiles per ordering group (see tile_coords), >= 1
   int32_t n_tt;  // token tiles
   int32_t n_vt;  // vocabulary tiles in this launch
@@ -194,6 +195,7 @@ struct DiagArgs {
   int32_t n_tt;
   int32_t n_vt;
   int32_t group_v;        // tile order: vocabulary tiles per group
+  int32_t ktail;          // as FusedArgs::ktail
   float* partials;        // [n_vt * kDiagParts][M*M + 3M][T]
   float* rowvals;         // [T][2*M*M]
   float* kl_pair;         // [M][M]
@@ -315,7 +317,7 @@ int gemm_wide_k_tile();  // K values per K-tile of the wide gradient GEMM
 int diag_tile_rows(bool wide);
 int diag_tile_cols(bool wide, int M);
 int diag_record_floats(int M);
-hipError_t launch_diag_tiles(const DiagArgs& a, bool f32, bool wide, hipStream_t stream);
+hipError_t launch_diag_tiles(const DiagArgs& a, bool f32, hipStream_t stream);
 hipError_t launch_diag_reduce(const DiagArgs& a, hipStream_t stream);
 hipError_t launch_diag_scatter(const DiagScatterArgs& a, hipStream_t stream);
 bool junction_shape(int64_t width, int* tpr, int* cpl);
@@ -323,11 +325,10 @@ int64_t junction_max_width();
 hipError_t launch_junction_fwd(const JunctionArgs& a, bool act_f32, hipStream_t stream);
 hipError_t launch_junction_bwd(const JunctionArgs& a, bool act_f32, bool grad_f32, hipStream_t stream);
 int head_tile();  // token rows of a head tile
-int head_tile_rows(bool wide, int n_tt);  // vocabulary rows of a head tile (128 or 192)
+int head_tile_rows(bool wide, int n_tt);  // wide: bf16; vocabulary rows of a head tile (128 or 192)
 int row_elems_per_thread(int64_t V);
-// rows: head_tile_rows(wide, a.n_tt) on the wide bf16 path, else 128 (checked)
-hipError_t launch_head_logits(const HeadArgs& a, bool f32, bool wide, int rows,
-                              hipStream_t stream);
+// rows: head_tile_rows(!f32, a.n_tt) (checked)
+hipError_t launch_head_logits(const HeadArgs& a, bool f32, int rows, hipStream_t stream);
 hipError_t launch_sample(const SampleArgs& a, int ept, hipStream_t stream);
 hipError_t launch_row_params(const RowParamArgs& a, int ept, hipStream_t stream);
 hipError_t launch_verify(const VerifyArgs& a, int ept, hipStream_t stream);
