@@ -2,9 +2,9 @@
 // sequence of the forward and backward passes (C ABI declared in mls.h).
 //
 // Forward:  fused tile kernel (partials) -> label logits -> row merge -> mean.
-// Backward: h_i^T once; then per vocabulary chunk of Vc rows:
-//           W_i[chunk]^T -> fused dlogits tile kernel (slab G, G^T)
-//           -> grad_W_i[chunk] = G^T h_i -> grad_h_i += G W_i[chunk].
+// Backward: per vocabulary chunk of Vc rows: fused dlogits tile kernel (slab G)
+//           -> grad_W_i[chunk] = G^T h_i and grad_h_i += G W_i[chunk]
+//           (the general bf16 path also writes G^T and transposes h_i and W_i).
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -177,8 +177,8 @@ void make_plan(const mls_problem* p, Plan& pl) {
   pl.wide = !pl.f32;
   for (int i = 0; i < p->M; ++i) pl.ktail = pl.ktail || p->d[i] % 64 != 0;
   pl.T_pad = round_up(p->T, kFusedBN);
-  pl.n_tt = (int)(pl.T_pad / kFusedBN);
-  const int fbm = fused_tile_rows(pl.wide);
+  pl.n_tt = (int)((p->T + fused_tile_cols(pl.f32) - 1) / fused_tile_cols(pl.f32));
+  const int fbm = fused_tile_rows(pl.f32);
   pl.n_vt_fwd = (int)((p->V + fbm - 1) / fbm);
   int64_t dmax = 0;
   for (int i = 0; i < p->M; ++i) dmax = std::max<int64_t>(dmax, p->d[i]);
@@ -227,7 +227,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
   const size_t slab = (size_t)pl.M * pl.T_pad * pl.Vc * pl.es;
   pl.off_slab = off;
   off = align256(off + slab);
-  if (!pl.wide_bwd) {  // general path: G^T slab and transposed operands as well
+  if (!pl.wide_bwd && !pl.f32) {  // general path: G^T slab and transposed operands as well
     pl.off_slabT = off;
     off = align256(off + slab);
     pl.off_hT = off;
@@ -370,6 +370,18 @@ void host_coeffs(int M, int s, float alpha, float tau, int mode, const float* w,
   }
 }
 
+// Output tile of the fp32 gradient GEMM: 64 x 64, or 32 x 32 with K split over
+// the block's waves where one chunk's launch has too few of the larger tiles to
+// fill the chip. Measured per launch, 32 against 64: 22 against 37 us at 120
+// tiles of 64 x 64 (T = 256, widths 128 / 256, chunks of 1,024), 48 against 71
+// at 258, 73 against 73 at 504, 102 against 109 at 696, 161 against 125 at 1,160.
+int f32_gemm_tile(const Plan& pl, const mls_problem* p) {
+  int64_t tiles = 0;
+  for (int i = 0; i < pl.M; ++i)
+    tiles += ((pl.T + 63) / 64 + (pl.Vc + 63) / 64) * ((p->d[i] + 63) / 64);
+  return tiles >= 900 ? 64 : 32;
+}
+
 // Label logits of every token and, when `count` is set, the valid-token count
 // into the statistics header (which the logit-gradient pass reads before the
 // loss mean is taken).
@@ -399,7 +411,7 @@ hipError_t forward_chunk(const mls_problem* p, const Plan& pl, int64_t t0, int64
   for (int i = 0; i < pl.M; ++i)
     a.h[i] = static_cast<const char*>(p->h[i]) + (size_t)t0 * p->d[i] * pl.es;
   a.T = tc;
-  a.n_tt = (int)((tc + kFusedBN - 1) / kFusedBN);
+  a.n_tt = (int)((tc + fused_tile_cols(pl.f32) - 1) / fused_tile_cols(pl.f32));
   // vocabulary tiles per group of the tile order, measured per token chunk:
   // 8 at 16 token tiles over 393 vocabulary tiles (2,048-token chunks at
   // V = 50,304; 4 and 16 are 5 % slower), 4 at 32 token tiles over 1,002
@@ -574,7 +586,8 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
   FusedArgs a;
   fill_common(p, pl, a);
   a.wide = pl.wide_bwd ? 1 : 0;
-  a.n_vt = (int)(pl.Vc / fused_tile_rows(pl.wide_bwd));
+  const int fbm = fused_tile_rows(pl.f32);
+  a.n_vt = (int)(pl.Vc / fbm);
   a.lse1 = sf;
   a.lset = sf + (int64_t)pl.M * pl.T;
   a.n_valid = reinterpret_cast<const int32_t*>(static_cast<const char*>(stats) + pl.header_off);
@@ -582,7 +595,8 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
   a.g_kl = g_kl;
   host_coeffs(pl.M, pl.s, p->alpha, p->tau, MLS_MODE_PAPER, nullptr, a.host_gce, a.host_gkl);
   a.slab = ws + pl.off_slab;
-  a.slabT = pl.wide_bwd ? nullptr : ws + pl.off_slabT;
+  const bool stored = pl.wide_bwd || pl.f32;  // products on the stored layouts
+  a.slabT = stored ? nullptr : ws + pl.off_slabT;
   char* hT = ws + pl.off_hT;
   char* WT = ws + pl.off_WT;
 
@@ -593,12 +607,13 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     acc += p->d[i];
   }
   const size_t slab_stride = (size_t)pl.T_pad * pl.Vc * pl.es;
-  const int tbm = gemm_tile_rows(pl.wide_bwd);
-  const int tbn = gemm_tile_cols(pl.wide_bwd);
+  int tbm = gemm_tile_rows(pl.wide_bwd);
+  int tbn = gemm_tile_cols(pl.wide_bwd);
+  if (pl.f32) tbm = tbn = f32_gemm_tile(pl, p);
   hipError_t e;
 
   // general path: h_i^T [d_i, T_pad] for the grad_W products
-  if (!pl.wide_bwd) {
+  if (!stored) {
     TransposeArgs ta;
     memset(&ta, 0, sizeof(ta));
     int64_t maxc = 0;
@@ -617,7 +632,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     }
     {
       ProfScope ps("transpose_h", s);
-      e = launch_transpose(ta, pl.T_pad, maxc, pl.f32, s);
+      e = launch_transpose(ta, pl.T_pad, maxc, s);
     }
     if (e != hipSuccess) return hip_fail(e, "transpose launch");
   }
@@ -627,7 +642,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     const int64_t vrows = std::min(pl.Vc, pl.V - v0);
 
     // general path: W_i[chunk]^T [d_i, Vc] for the grad_h products
-    if (!pl.wide_bwd) {
+    if (!stored) {
     TransposeArgs ta;
     memset(&ta, 0, sizeof(ta));
     int64_t maxc = 0;
@@ -646,18 +661,18 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     }
     {
       ProfScope ps("transpose_W", s);
-      e = launch_transpose(ta, pl.Vc, maxc, pl.f32, s);
+      e = launch_transpose(ta, pl.Vc, maxc, s);
     }
     if (e != hipSuccess) return hip_fail(e, "transpose launch");
     }
 
     a.v0 = v0;
-    if (pl.wide_bwd) {
+    if (stored) {
       // The wide GEMM reads slab columns past the chunk's rows only up to the
       // K-tile holding its last row (grad_h) or for output rows it does not
-      // store (grad_W), so the vocabulary tiles past the chunk end are skipped.
-      const int bm = fused_tile_rows(true);
-      if (bm % gemm_wide_k_tile() == 0) a.n_vt = (int)((vrows + bm - 1) / bm);
+      // store (grad_W), the fp32 one only in whole 16-byte chunks, so the
+      // vocabulary tiles past the chunk end are skipped.
+      if (pl.f32 || fbm % gemm_wide_k_tile() == 0) a.n_vt = (int)((vrows + fbm - 1) / fbm);
     }
     {
       ProfScope ps("fused_bwd", s);
@@ -678,7 +693,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       g.A = static_cast<const char*>(a.slab) + (size_t)i * slab_stride;
       g.lda = pl.Vc;
       g.rows = pl.T;
-      if (pl.wide_bwd) {
+      if (stored) {
         g.B = static_cast<const char*>(p->W[i]) + (size_t)v0 * p->d[i] * pl.es;  // [v][d]
         g.ldb = p->d[i];
         g.cols = vrows;
@@ -710,7 +725,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       // the chunk's rows past vrows read as zero from the head: the last,
       // shorter chunk stops at the K-tile holding its last row
       const int64_t kt = gemm_wide_k_tile();
-      g.K = pl.wide_bwd ? std::min(pl.Vc, (vrows + kt - 1) / kt * kt) : pl.Vc;
+      g.K = pl.f32 ? vrows : pl.wide_bwd ? std::min(pl.Vc, (vrows + kt - 1) / kt * kt) : pl.Vc;
       g.kind = 0;
       g.tiles_m = (int)((pl.T + tbm - 1) / tbm);
       g.tiles_n = (int)((p->d[i] + tbn - 1) / tbn);
@@ -722,7 +737,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     for (int i = 0; i < pl.M; ++i) {
       if (!grad_W[i]) continue;
       GemmGroup& g = ga.g[ga.ngroups++];
-      if (pl.wide_bwd) {
+      if (stored) {
         g.A = static_cast<const char*>(a.slab) + (size_t)i * slab_stride;  // [t][v]
         g.lda = pl.Vc;
         g.rows = pl.T_pad;
@@ -740,7 +755,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       g.C = grad_W[i] + v0 * p->d[i];
       g.ldc = p->d[i];
       g.ldc_rows = vrows;
-      g.K = pl.T_pad;
+      g.K = pl.f32 ? pl.T : pl.T_pad;
       g.kind = 1;
       g.tiles_m = (int)((vrows + tbm - 1) / tbm);
       g.tiles_n = (int)((p->d[i] + tbn - 1) / tbn);
@@ -762,7 +777,8 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     }
     {
       ProfScope ps("gemm_grads", s);
-      e = pl.wide_bwd ? launch_gemm_wide(ga, tiles, s) : launch_gemm_nt(ga, tiles, pl.f32, s);
+      e = pl.f32 ? launch_gemm_f32(ga, tbm, tiles, s)
+                 : pl.wide_bwd ? launch_gemm_wide(ga, tiles, s) : launch_gemm_nt(ga, tiles, s);
     }
     if (e != hipSuccess) return hip_fail(e, "gradient GEMM launch");
   }

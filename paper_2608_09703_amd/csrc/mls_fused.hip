@@ -31,7 +31,12 @@ namespace {
 // is not a multiple of the 64-wide K-tile, and the general one (fp32; bf16 only
 // where the wide backward's 32-bit offsets do not reach).
 using GenMmaBf16 = TileMma<Bf16, kFusedBM, kFusedBN, 2, 2>;
-using GenMmaF32 = TileMma<F32, kFusedBM, kFusedBN, 2, 2>;
+// fp32: 64 x 64, which keeps the matrix cores fed (a K-tile's MFMAs last longer
+// than its loads) and gives a small problem four times the blocks of 128 x 128
+// (T = 256, widths 128 / 256, V = 4,096: forward 36 -> 16 us, backward tiles
+// 43 -> 18 us per chunk; T = 2,048, widths 256 / 512 / 512, V = 16,384: the whole
+// forward and backward 3,650 -> 3,260 us).
+using MmaF32 = TileMma<F32, kFusedF32, kFusedF32, 2, 2>;
 using WideFused = WideMma<kFusedWideBM, kFusedBN, 2, 2, 2>;  // 2 blocks per CU
 using WideFusedTail =
     WideMma<kFusedWideBM, kFusedBN, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(Mma::NT, MINB) void fused_fwd_kernel(FusedArgs a) {
   constexpr int FM = Mma::FM;
   constexpr int FN = Mma::FN;
   static_assert(WGM == kFusedFwdParts, "one partial record per wave row");
-  static_assert(BN == kFusedBN, "partial records are grouped by token tile");
+  static_assert(kFusedBN % BN == 0, "a tile's tokens lie in one record group");
   __shared__ __attribute__((aligned(16))) char smem[Mma::kSmemBytes];
 
   const int tid = threadIdx.x;
@@ -100,8 +105,9 @@ __global__ __launch_bounds__(Mma::NT, MINB) void fused_fwd_kernel(FusedArgs a) {
   const int64_t tbase = (int64_t)tt * BN;
   const bool full = vbase + BM <= a.V;
   const float ct = kLog2e * a.inv_tau;
-  // records of sub-model order[oi] and token tile tt: [n_vt * WGM][BN]
+  // records of sub-model order[oi] and token group tbase / kFusedBN: [n_vt * WGM][kFusedBN]
   const int64_t n_rec = (int64_t)a.n_vt * WGM;
+  const int64_t n_tg = (a.T + kFusedBN - 1) / kFusedBN;
   const int64_t rec = (int64_t)vt * WGM + wm;
 
   // teacher weights exp((l_s - max_s) / tau); 0 outside V
@@ -233,7 +239,8 @@ __global__ __launch_bounds__(Mma::NT, MINB) void fused_fwd_kernel(FusedArgs a) {
       // 3. the wave's partial record of this token
       const int c = Mma::col_of(wn, fn, lane);
       if (hi == 0 && tbase + c < a.T)
-        a.partials[(((int64_t)oi * a.n_tt + tt) * n_rec + rec) * BN + c] = make_float4(mb, s1, st, xr);
+        a.partials[((oi * n_tg + tbase / kFusedBN) * n_rec + rec) * kFusedBN + tbase % kFusedBN + c] =
+            make_float4(mb, s1, st, xr);
     }
   }
 }
@@ -254,6 +261,8 @@ __device__ __forceinline__ void store4<F32>(float* p, float a0, float a1, float 
   *reinterpret_cast<float4*>(p) = make_float4(a0, a1, a2, a3);
 }
 
+// Backward tile kernel of the fp32 path (one slab, token-major) and of the
+// general bf16 path (both slab layouts).
 template <class Mma, typename E, bool TAU1>
 __global__ __launch_bounds__(Mma::NT, 1) void fused_bwd_kernel(FusedArgs a) {
   constexpr int BM = Mma::kBM;
@@ -344,9 +353,11 @@ __global__ __launch_bounds__(Mma::NT, 1) void fused_bwd_kernel(FusedArgs a) {
           }
           const int row0 = Mma::row_of(wm, fm, rg * 4, lane);
           store4<E>(slab + t * a.Vc + vloc + row0, g[0], g[1], g[2], g[3]);
+          if (E::kBytes == 2) {
 #pragma unroll
-          for (int rr = 0; rr < 4; ++rr)
-            slabT[(vloc + row0 + rr) * a.T_pad + t] = to_storage<E>(g[rr]);
+            for (int rr = 0; rr < 4; ++rr)
+              slabT[(vloc + row0 + rr) * a.T_pad + t] = to_storage<E>(g[rr]);
+          }
         }
     }
   }
@@ -513,13 +524,15 @@ hipError_t launch_bwd_t(const FusedArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-int fused_tile_rows(bool wide) { return wide ? kFusedWideBM : kFusedBM; }
+static_assert(kFusedWideBM == kFusedBM, "both bf16 cores have one tile");
+int fused_tile_rows(bool f32) { return f32 ? kFusedF32 : kFusedBM; }
+int fused_tile_cols(bool f32) { return f32 ? kFusedF32 : kFusedBN; }
 
 hipError_t launch_fused_fwd(const FusedArgs& a, bool f32, hipStream_t stream) {
   const bool tau1 = a.tau == 1.0f;
   if (f32)
-    return tau1 ? launch_fwd_t<GenMmaF32, F32, true>(a, stream)
-                : launch_fwd_t<GenMmaF32, F32, false>(a, stream);
+    return tau1 ? launch_fwd_t<MmaF32, F32, true>(a, stream)
+                : launch_fwd_t<MmaF32, F32, false>(a, stream);
   // bf16: the wide core for every width. K tails (widths that are not multiples
   // of 64) have their own form, so that the loads of the others carry no masks:
   // at T = 1,531, widths 200 / 408 / 1,000, V = 32,003, tau = 2 the forward
@@ -535,8 +548,8 @@ hipError_t launch_fused_fwd(const FusedArgs& a, bool f32, hipStream_t stream) {
 hipError_t launch_fused_bwd(const FusedArgs& a, bool f32, hipStream_t stream) {
   const bool tau1 = a.tau == 1.0f;
   if (f32)
-    return tau1 ? launch_bwd_t<GenMmaF32, F32, true>(a, stream)
-                : launch_bwd_t<GenMmaF32, F32, false>(a, stream);
+    return tau1 ? launch_bwd_t<MmaF32, F32, true>(a, stream)
+                : launch_bwd_t<MmaF32, F32, false>(a, stream);
   if (a.wide)
     return a.ktail ? launch_bwd_wide<WideFusedTail>(a, stream) : launch_bwd_wide<WideFused>(a, stream);
   return tau1 ? launch_bwd_t<GenMmaBf16, Bf16, true>(a, stream)

@@ -1,10 +1,10 @@
 // The two backward products of the LM head (the head is linear, paper
-// section 2, "Modeling"), per vocabulary chunk, both products for every
-// sub-model in one grouped launch:
-//   grad_W_i[chunk] = G_i^T h_i       A = G_i^T slab [Vc, T_pad], B = h_i^T [d_i, T_pad]
-//   grad_h_i       += G_i W_i[chunk]  A = G_i slab   [T_pad, Vc], B = W_i[chunk]^T [d_i, Vc]
-// Both are NT tile products on the shared MFMA main loop; the transposed
-// operands h_i^T and W_i[chunk]^T are produced by the transpose kernel below.
+// section 2, "Modeling"), both products for every sub-model in one grouped launch:
+//   grad_W_i[chunk] = G_i^T h_i
+//   grad_h_i       += G_i W_i[chunk]
+// The bf16 and fp32 kernels read the slab G [t][v], h [t][d] and the head [v][d]
+// as they are stored; the general bf16 kernel is an NT tile product whose
+// transposed operands come from the transpose kernel below.
 #include "mls_core.h"
 #include "mls_device.h"
 #include "mls_launch.h"
@@ -25,8 +25,9 @@ __device__ __forceinline__ void store_out(const GemmGroup& g, int64_t idx, float
   }
 }
 
-template <typename E>
+// General bf16 path (operands of 4 GiB and more): pre-transposed operands.
 __global__ __launch_bounds__(kThreads, 2) void gemm_nt_kernel(GemmArgs a) {
+  using E = Bf16;
   using Mma = TileMma<E, kGemmBM, kGemmBN, 2, 2>;
   constexpr int FM = Mma::FM;
   constexpr int FN = Mma::FN;
@@ -64,6 +65,152 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_nt_kernel(GemmArgs a) {
         if (m < g.rows && n < g.cols) store_out(g, m * g.ldc + n, mma.acc[fm][fn][r]);
       }
     }
+}
+
+// fp32 path: the slab, the head chunk and h are read in their stored layouts.
+// v_mfma_f32_32x32x2_f32 takes one fp32 of A and of B per lane, A[m = l % 32][k
+// = l / 32], so a K-tile kept in LDS as [k][m] rows feeds it with plain 4-byte
+// reads of consecutive lanes: an M-contiguous operand (the head chunk, h, and
+// the slab for grad_W) is stored as it is loaded and only the K-contiguous one
+// (the slab for grad_h) is transposed on its way into LDS, so neither transposed
+// copies in memory nor a second slab layout are needed. Four waves: a 2 x 2
+// grid of 32 x 32 tiles (KS = 1), or, for launches with too few tiles to fill
+// the chip, one 32 x 32 tile whose K-tiles the waves take a quarter each of
+// (KS = 4; the four sums are added in wave order, so results are reproducible).
+// At T = 256, widths 128 / 256, V = 4,096 (30 blocks of 128 x 128 before) a
+// chunk's products take 20 us instead of 90, and the transposed copies' 9 us go.
+template <int BM, int BN, int BK>
+struct F32Tile {
+  static constexpr int LDA = BM + 2;  // row length: transposed 4-byte stores hit distinct banks
+  static constexpr int LDB = BN + 2;
+  float a[BK * LDA];
+  float b[BK * LDB];
+};
+
+// 16-byte chunks of a K-tile [k0, k0 + BK) x [m0, m0 + ROWS) of an operand held
+// by one thread: KC [m][k] (rows: m extent, K: k extent), MC [k][m] (rows: k
+// extent, K: m extent). Chunks past either extent are 0.
+template <int ROWS, int BK, bool MC>
+struct F32Loader {
+  static constexpr int kChunks = ROWS * BK / 4 / kThreads;
+  static constexpr int kPer = MC ? ROWS / 4 : BK / 4;  // chunks per stored row
+  float4 r[kChunks];
+  __device__ __forceinline__ void load(const float* __restrict__ base, int64_t ld, int64_t m0,
+                                       int64_t m_ext, int64_t k0, int64_t k_ext, int tid) {
+#pragma unroll
+    for (int j = 0; j < kChunks; ++j) {
+      const int ci = tid + kThreads * j;
+      const int64_t row = (MC ? k0 : m0) + ci / kPer;
+      const int64_t col = (MC ? m0 : k0) + ci % kPer * 4;
+      const bool in = row < (MC ? k_ext : m_ext) && col < (MC ? m_ext : k_ext);
+      r[j] = in ? *reinterpret_cast<const float4*>(base + row * ld + col)
+                : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  template <int LD>
+  __device__ __forceinline__ void store(float* lds, int tid) const {
+#pragma unroll
+    for (int j = 0; j < kChunks; ++j) {
+      const int ci = tid + kThreads * j;
+      const int row = ci / kPer;
+      const int col = ci % kPer * 4;
+      const float v[4] = {r[j].x, r[j].y, r[j].z, r[j].w};
+      if (MC) {
+        *reinterpret_cast<float2*>(lds + row * LD + col) = make_float2(v[0], v[1]);
+        *reinterpret_cast<float2*>(lds + row * LD + col + 2) = make_float2(v[2], v[3]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lds[(col + q) * LD + row] = v[q];
+      }
+    }
+  }
+};
+
+template <int BM, int BN, int KS, bool AMC>
+__device__ __forceinline__ void f32_tile(const GemmGroup& g, int tm, int tn, char* smem, int tid) {
+  constexpr int BK = 32 * KS;
+  using Tile = F32Tile<BM, BN, BK>;
+  Tile* stage = reinterpret_cast<Tile*>(smem);
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int wm = KS > 1 ? 0 : wave & 1;
+  const int wn = KS > 1 ? 0 : wave >> 1;
+  const int kw = KS > 1 ? wave * 32 : 0;  // the wave's part of a K-tile
+  const int64_t m0 = (int64_t)tm * BM;
+  const int64_t n0 = (int64_t)tn * BN;
+  const int64_t mext = g.ldc_rows, next = g.ldc, K = g.K;
+  const float* A = static_cast<const float*>(g.A);
+  const float* B = static_cast<const float*>(g.B);
+  f32x16_t acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  F32Loader<BM, BK, AMC> la;
+  F32Loader<BN, BK, true> lb;
+  const int64_t nk = (K + BK - 1) / BK;
+  la.load(A, g.lda, m0, mext, 0, K, tid);
+  lb.load(B, g.ldb, n0, next, 0, K, tid);
+  la.template store<Tile::LDA>(stage[0].a, tid);
+  lb.template store<Tile::LDB>(stage[0].b, tid);
+  __syncthreads();
+  const int ml = wm * 32 + (lane & 31);
+  const int nl = wn * 32 + (lane & 31);
+  for (int64_t kt = 0; kt < nk; ++kt) {
+    const bool more = kt + 1 < nk;
+    if (more) {
+      la.load(A, g.lda, m0, mext, (kt + 1) * BK, K, tid);
+      lb.load(B, g.ldb, n0, next, (kt + 1) * BK, K, tid);
+    }
+    const Tile& t = stage[kt & 1];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const int k = kw + 2 * s + (lane >> 5);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(t.a[k * Tile::LDA + ml], t.b[k * Tile::LDB + nl],
+                                                 acc, 0, 0, 0);
+    }
+    if (more) {
+      Tile& nx = stage[(kt + 1) & 1];
+      la.template store<Tile::LDA>(nx.a, tid);
+      lb.template store<Tile::LDB>(nx.b, tid);
+    }
+    __syncthreads();
+  }
+  if (KS > 1) {  // the waves' sums, through LDS
+    float* part = reinterpret_cast<float*>(smem);
+    if (wave > 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[((wave - 1) * 16 + r) * 64 + lane] = acc[r];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 0; w < KS - 1; ++w)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] += part[(w * 16 + r) * 64 + lane];
+  }
+  const int64_t n = n0 + nl;
+  if (n >= next) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int64_t m = m0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (m < mext) store_out(g, m * g.ldc + n, acc[r]);
+  }
+}
+
+template <int BM, int BN, int KS>
+__global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmArgs a) {
+  __shared__ __attribute__((aligned(16))) char smem[2 * sizeof(F32Tile<BM, BN, 32 * KS>)];
+  const int b = blockIdx.x;
+  int gi = 0;
+  for (int k = 1; k < a.ngroups; ++k)
+    if (b >= a.g[k].tile_begin) gi = k;
+  const GemmGroup& g = a.g[gi];
+  const int local = b - g.tile_begin;
+  const int tn = local % g.tiles_n;
+  const int tm = local / g.tiles_n;
+  if (g.kind == 0)
+    f32_tile<BM, BN, KS, false>(g, tm, tn, smem, threadIdx.x);
+  else
+    f32_tile<BM, BN, KS, true>(g, tm, tn, smem, threadIdx.x);
 }
 
 // bf16 path: 256 x 256 tiles, 8 waves (2 per SIMD), direct-to-LDS loads, 2
@@ -293,8 +440,8 @@ __global__ __launch_bounds__(MmaH::NT, 1) void gemm_wide_kernel(GemmArgs a, int 
     wide_tile<MmaW>(g, tm, tn, mext, next, smem, threadIdx.x);
 }
 
-template <typename S>
 __global__ __launch_bounds__(kThreads) void transpose_kernel(TransposeArgs a) {
+  using S = uint16_t;
   const TransposeJob& j = a.j[blockIdx.z];
   const int64_t rb = (int64_t)blockIdx.x * 64;
   const int64_t cb = (int64_t)blockIdx.y * 64;
@@ -332,24 +479,29 @@ hipError_t launch_gemm_wide(const GemmArgs& a, int total_tiles, hipStream_t stre
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_nt(const GemmArgs& a, int total_tiles, bool f32, hipStream_t stream) {
+hipError_t launch_gemm_f32(const GemmArgs& a, int tile, int total_tiles, hipStream_t stream) {
   if (total_tiles <= 0) return hipSuccess;
-  if (f32)
-    hipLaunchKernelGGL(gemm_nt_kernel<F32>, dim3(total_tiles), dim3(kThreads), 0, stream, a);
+  if (tile == 64)
+    hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 1>), dim3(total_tiles), dim3(kThreads), 0, stream, a);
+  else if (tile == 32)
+    hipLaunchKernelGGL((gemm_f32_kernel<32, 32, 4>), dim3(total_tiles), dim3(kThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(gemm_nt_kernel<Bf16>, dim3(total_tiles), dim3(kThreads), 0, stream, a);
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_nt(const GemmArgs& a, int total_tiles, hipStream_t stream) {
+  if (total_tiles <= 0) return hipSuccess;
+  hipLaunchKernelGGL(gemm_nt_kernel, dim3(total_tiles), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
 hipError_t launch_transpose(const TransposeArgs& a, int64_t max_out_rows, int64_t max_cols,
-                            bool f32, hipStream_t stream) {
+                            hipStream_t stream) {
   if (a.njobs <= 0) return hipSuccess;
   dim3 grid((unsigned)((max_out_rows + 63) / 64), (unsigned)((max_cols + 63) / 64),
             (unsigned)a.njobs);
-  if (f32)
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(kThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(kThreads), 0, stream, a);
+  hipLaunchKernelGGL(transpose_kernel, grid, dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 

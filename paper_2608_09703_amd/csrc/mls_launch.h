@@ -14,8 +14,10 @@ constexpr int kMaxModels = 8;
 // Tile of the fused logits kernels: BM vocabulary rows x BN token columns.
 constexpr int kFusedBM = 128;      // general core
 constexpr int kFusedWideBM = 128;  // wide bf16 core
+constexpr int kFusedF32 = 64;      // fp32 core, rows and columns
 // forward partial records per (vocabulary tile, token, sub-model): one per
-// wave row of the tile, each over its own half of the tile's rows
+// wave row of the tile, each over its own half of the tile's rows; their
+// records are grouped by kFusedBN tokens whatever the tile's columns
 constexpr int kFusedFwdParts = 2;
 // diagnostics records per (vocabulary tile, token), one per wave row likewise
 constexpr int kDiagParts = 2;
@@ -50,7 +52,7 @@ struct FusedArgs {
   int32_t n_tt;  // token tiles
   int32_t n_vt;  // vocabulary tiles in this launch
   // forward
-  float4* partials;  // [M (processing order)][n_tt][n_vt * kFusedFwdParts][kFusedBN]
+  float4* partials;  // [M (processing order)][ceil(T / kFusedBN)][n_vt * kFusedFwdParts][kFusedBN]
   // forward of the fused forward + backward: every logit, as fp16 of its
   // distance to its partial record's maximum, [M (sub-model index)][n_tt * BN][ld_lslab]
   uint16_t* lslab;
@@ -91,7 +93,7 @@ struct GemmGroup {
   int32_t tile_begin;
   int32_t accumulate;
   int32_t group_m;  // tile order: 0 = n fastest; g > 0 = groups of g row tiles, rows fastest
-  // bf16 wide path only: operand layouts. 0: A is [m][k], B is [k][n] (grad_h:
+  // bf16 wide and fp32 paths: operand layouts. 0: A is [m][k], B is [k][n] (grad_h:
   // slab [t][v] times a head chunk [v][d]); 1: A is [k][m], B is [k][n] (grad_W:
   // slab [t][v] as [k=t][m=v] times h [t][d]). rows/cols are the stored row counts
   // of A/B for these layouts (see WideMma::run).
@@ -302,7 +304,8 @@ int64_t mfma_probe_sink_floats();
 mls_status set_error(mls_status s, const char* what, const char* detail);
 
 // Launchers (each enqueues on `stream` and returns the launch status).
-int fused_tile_rows(bool wide);
+int fused_tile_rows(bool f32);
+int fused_tile_cols(bool f32);
 hipError_t launch_fused_fwd(const FusedArgs& a, bool f32, hipStream_t stream);
 hipError_t launch_fused_bwd(const FusedArgs& a, bool f32, hipStream_t stream);
 // Output tile of the backward GEMMs (wide bf16 path or the general path).
@@ -310,9 +313,11 @@ int gemm_tile_rows(bool wide);
 int gemm_tile_cols(bool wide);
 // Wide bf16 path: grad_h and grad_W products read in stored layouts.
 hipError_t launch_gemm_wide(const GemmArgs& a, int total_tiles, hipStream_t stream);
-hipError_t launch_gemm_nt(const GemmArgs& a, int total_tiles, bool f32, hipStream_t stream);
+// fp32 path, stored layouts; tile 64 or 32 (rows and columns of a block's output)
+hipError_t launch_gemm_f32(const GemmArgs& a, int tile, int total_tiles, hipStream_t stream);
+hipError_t launch_gemm_nt(const GemmArgs& a, int total_tiles, hipStream_t stream);
 hipError_t launch_transpose(const TransposeArgs& a, int64_t max_out_rows, int64_t max_cols,
-                            bool f32, hipStream_t stream);
+                            hipStream_t stream);
 int gemm_wide_k_tile();  // K values per K-tile of the wide gradient GEMM
 int diag_tile_rows(bool wide);
 int diag_tile_cols(bool wide, int M);
