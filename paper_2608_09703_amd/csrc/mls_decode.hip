@@ -128,20 +128,31 @@ __global__ __launch_bounds__(Mma::NT, 2) void head_logits_kernel(HeadArgs a) {
 //
 // Nucleus threshold. With `total` the sum of the row's exp weights and
 // P = top_p * total, theta is the largest weight value whose mass
-// S(theta) = sum(weight >= theta) still reaches P. Two facts bound it:
-// * S(c) >= P implies theta >= c (theta is the largest such value);
-// * for c' > c, S(c') >= S(c) - n(c) c', where n(c) counts the weights at or
-//   above c; so S(c) >= P also gives theta >= (S(c) - P) / n(c).
-// The search starts at c0 = (1 - top_p) total / V (the weights below c0 hold
-// less than (1 - top_p) of the mass, so S(c0) >= P). The candidates
-// {weight >= c0} are compacted once into a first LDS list (each wave its own
-// region, in index order), the bound is raised with the second fact on that
-// list, and the survivors move in index order to the final list. One wave
-// then finds theta over the fp32 bit pattern (positive floats order like
-// their bits) with four-way steps, resolves ties and draws: every kept token
-// is in the final list. Rows whose first list overflows raise the bound over
-// the row's registers instead; rows whose candidate set stays large (flat
-// distributions) take a block-wide search over the whole row.
+// S(theta) = sum(weight >= theta) still reaches P. S(c) >= P for some c puts
+// theta at c or above, and every kept token among the weights >= c.
+// 1. A close c for the price of a few LDS atomics: the largest weight of each
+//    of a thread's kGroups runs of elements (4,096 in a row) enters a histogram
+//    of mass over the weights' upper bits. From the top down, the first bin
+//    edge c at which these maxima alone hold P has S(c) >= P, and where the
+//    nucleus is small against the number of runs, c lies little below theta.
+// 2. The weights >= c, a few per wave, move in index order to an LDS list; one
+//    wave finds theta among them, resolves ties and draws.
+// 3. Rows whose nucleus is too large for step 1 or the list take a radix
+//    selection over all weights >= c0 = (1 - top_p) total / V (the weights
+//    below c0 hold less than (1 - top_p) of the mass): a histogram of 64-bit
+//    fixed-point masses (2^-44; sums do not depend on the order of the atomics)
+//    over eight bins per octave names the bin that holds theta; if the weights
+//    from that bin's lower edge up still overflow the list, three more levels
+//    over the remaining bits give theta itself.
+//
+// The kernel lasts as long as one row's serial chain on its CU: load and
+// maximum 4.7 us at V = 49,152, exp weights and sum 2.7 us (both bound by the
+// CU), then barriers, scans of the thread's elements and the list wave. At 102
+// such rows (nucleus 0.9 at temperature 0.4) a launch took 24 us with a list of
+// every weight >= c0 (some 2,000 of them), three bound raises on it and a
+// four-way threshold search, and 22 us with the radix selection for every row;
+// it takes 15.5 us (one row: 20 -> 12 us; the records of 714 verifier rows:
+// 73 -> 51 us).
 
 constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / 64;
@@ -149,9 +160,13 @@ constexpr int kMaxEPT = 64;
 constexpr int kRunMax = 16;              // candidate entries per lane of the list wave
 constexpr int kMaxCand = 64 * kRunMax;   // candidates one wave holds
 constexpr int kSmallCand = 4 * 64;       // lists searched with 4 entries per lane
-constexpr int kBigCand = 4 * kRowThreads;  // first list: 4 entries per thread
-constexpr int kRegion = kBigCand / kRowWaves;  // first-list entries per wave
-constexpr int kBoundRounds = 3;          // raises of the lower bound
+constexpr int kGroups = 4;               // runs of a thread's elements with a maximum each
+constexpr int kRegion = 256;             // list entries per wave before they are joined
+constexpr int kMaxShift = 21;            // bins of the maxima: four per octave,
+constexpr int kMaxBins = 64;             // 16 octaves (the last bin: everything below)
+constexpr int kTopShift = 20;            // radix selection: the bits from here up,
+constexpr int kBins = 512;               // weights down to 2^-64 (c0 >= 2^-40)
+constexpr uint32_t kOne = 0x3f800000u;   // weight 1, the largest
 
 // LDS slot of list entry j: one gap after every 16 entries, so that the lanes
 // of the list wave, each reading a run of consecutive entries, hit different
@@ -160,11 +175,16 @@ __device__ __forceinline__ int cand_slot(int j) { return j + (j >> 4); }
 constexpr int kCandSlots = kMaxCand + kMaxCand / 16;
 
 struct RowShared {
-  float bw[kBigCand];             // first list (weights >= c0): one region per wave,
-  int bi[kBigCand];               // each in index order
-  float cw[kCandSlots];           // final list, index order
+  unsigned long long hist[kBins]; // mass per bin, 2^-44
+  unsigned maxhist[kMaxBins];     // mass of the runs' maxima per bin, 2^-15
+  float bw[kRowWaves * kRegion];  // one list region per wave, in index order
+  int bi[kRowWaves * kRegion];
+  float cw[kCandSlots];           // candidate list, index order
   int ci[kCandSlots];             // their vocabulary indices
   float seg[kMaxEPT * kRowWaves]; // per (wave, slab) sums for whole-row index-order scans
+  float scr[64];                  // list wave: the threshold bin's entries
+  float rmax[kRowWaves];
+  float rsum[kRowWaves];
   float red[kRowWaves];
   int ired[kRowWaves];
   int wcnt[kRowWaves];            // per-wave list counts
@@ -208,56 +228,20 @@ __device__ __forceinline__ int block_count(int v, RowShared& sh) {
   __syncthreads();
   return s;
 }
-__device__ __forceinline__ void block_sum2(float& f, int& n, RowShared& sh) {
-  f = wave_sum(f);
-  n = wave_sum(n);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    sh.red[w] = f;
-    sh.ired[w] = n;
-  }
-  __syncthreads();
-  float s = 0.f;
-  int c = 0;
-#pragma unroll
-  for (int i = 0; i < kRowWaves; ++i) {
-    s += sh.red[i];
-    c += sh.ired[i];
-  }
-  __syncthreads();
-  f = s;
-  n = c;
-}
-// As block_sum2, with n already the wave's total in every lane.
-__device__ __forceinline__ void block_sum2w(float& f, int& n, RowShared& sh) {
-  f = wave_sum(f);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    sh.red[w] = f;
-    sh.ired[w] = n;
-  }
-  __syncthreads();
-  float s = 0.f;
-  int c = 0;
-#pragma unroll
-  for (int i = 0; i < kRowWaves; ++i) {
-    s += sh.red[i];
-    c += sh.ired[i];
-  }
-  __syncthreads();
-  f = s;
-  n = c;
-}
-__device__ __forceinline__ float block_max(float v, RowShared& sh) {
+// The waves' results, one per lane of each 16-lane row, combined in a fixed
+// order. Used with an LDS array of its own each time, so one barrier suffices.
+static_assert(kRowWaves == 16, "one DPP row holds the waves' results");
+__device__ __forceinline__ float block_max_once(float v, float* red) {
   v = wave_max(v);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh.red[w] = v;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  float s = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < kRowWaves; ++i) s = fmaxf(s, sh.red[i]);
+  return wave_max(red[threadIdx.x & 15]);
+}
+__device__ __forceinline__ float block_sum_once(float v, float* red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  return s;
+  return row16_sum(red[threadIdx.x & 15]);
 }
 
 // Argmax with the lowest index on ties.
@@ -392,62 +376,36 @@ __device__ __forceinline__ bool kept_w(float e, int v, const RowDist& d) {
   return e > d.theta || (e == d.theta && e > 0.f && v <= d.tie_cut);
 }
 
-// Writes the row elements with flag(i) set to an LDS list in index order
-// (weight val(i) to dw, vocabulary index to di; at cand_slot(position) when
-// PAD) and returns how many there are; entries beyond CAP are not written.
-// Index order is (wave, slab, lane): a first pass counts each wave's
-// elements, then every wave writes from the sum of the counts before it.
-template <int EPT, int CAP, bool PAD, class Flag, class Val>
-__device__ __forceinline__ int compact_row(Flag flag, Val val, float* dw, int* di,
-                                           RowShared& sh) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  int cnt = 0;  // wave-uniform
+// Keeps the compiler from carrying compares of the thread's elements (a mask of
+// two scalar registers each) from one pass over them to the next: it would
+// spill them.
+template <int EPT>
+__device__ __forceinline__ void pass_fence(float* w) {
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) cnt += __builtin_popcountll(__ballot(flag(i)));
-  if (lane == 0) sh.wcnt[wave] = cnt;
-  __syncthreads();
-  int pos0 = 0, total = 0;
-#pragma unroll
-  for (int k = 0; k < kRowWaves; ++k) {
-    pos0 += k < wave ? sh.wcnt[k] : 0;
-    total += sh.wcnt[k];
-  }
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const bool f = flag(i);
-    const unsigned long long b = __ballot(f);
-    if (f) {
-      const int pos = pos0 + lanes_below(b);
-      if (pos < CAP) {
-        const int sl = PAD ? cand_slot(pos) : pos;
-        dw[sl] = val(i);
-        di[sl] = elem_v<EPT>(i);
-      }
-    }
-    pos0 += __builtin_popcountll(b);
-  }
-  __syncthreads();
-  return total;
+  for (int i = 0; i < EPT; ++i) asm volatile("" : "+v"(w[i]));
 }
 
-// One pass: each wave writes its flagged elements, in index order, to its own
-// region of kRegion entries of the first list (bw, bi); the counts go to
-// sh.wcnt. Returns the total; `fits` tells whether every wave's elements fit
-// its region.
-template <int EPT, class Flag, class Val>
-__device__ __forceinline__ int compact_regions(Flag flag, Val val, RowShared& sh, bool& fits) {
+// Writes the row elements of bit patterns >= lo (lo > 0, no negative elements)
+// to the LDS list in index order, at cand_slot(position), and returns how many
+// there are. Index order is (wave, slab, lane): each wave writes its elements to
+// its own region, then moves them behind those of the waves before it. Where
+// the total exceeds kMaxCand or a wave's number its region, nothing is moved
+// and a number above kMaxCand is returned.
+template <int EPT>
+__device__ __forceinline__ int compact_row(float* w, uint32_t lo, RowShared& sh) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
+  pass_fence<EPT>(w);
   int pos0 = 0;  // wave-uniform
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const bool f = flag(i);
+    const bool f = __float_as_uint(w[i]) >= lo;
     const unsigned long long b = __ballot(f);
+    if (b == 0) continue;  // most slabs hold no entry
     if (f) {
       const int pos = pos0 + lanes_below(b);
       if (pos < kRegion) {
-        sh.bw[wave * kRegion + pos] = val(i);
+        sh.bw[wave * kRegion + pos] = w[i];
         sh.bi[wave * kRegion + pos] = elem_v<EPT>(i);
       }
     }
@@ -455,13 +413,16 @@ __device__ __forceinline__ int compact_regions(Flag flag, Val val, RowShared& sh
   }
   if (lane == 0) sh.wcnt[wave] = pos0;
   __syncthreads();
-  int total = 0;
-  fits = true;
-#pragma unroll
-  for (int k = 0; k < kRowWaves; ++k) {
-    total += sh.wcnt[k];
-    fits = fits && sh.wcnt[k] <= kRegion;
+  const int cnt = sh.wcnt[lane & (kRowWaves - 1)];  // the 16 counts, in every lane row
+  const int incl = row16_incl_scan(cnt);
+  const int total = lane_read(incl, kRowWaves - 1);
+  if (total > kMaxCand || __ballot(cnt > kRegion) != 0) return kMaxCand + 1;
+  const int at = wave == 0 ? 0 : lane_read(incl, wave - 1);
+  for (int j = lane; j < pos0; j += 64) {
+    sh.cw[cand_slot(at + j)] = sh.bw[wave * kRegion + j];
+    sh.ci[cand_slot(at + j)] = sh.bi[wave * kRegion + j];
   }
+  __syncthreads();
   return total;
 }
 
@@ -514,76 +475,63 @@ __device__ __forceinline__ int run_draw(const float (&kw)[RUN], float target) {
   return __builtin_amdgcn_readlane(j, L);
 }
 
-// Theta from the final list (list wave; n entries, weights >= c with
-// S(c) >= P): the largest bit pattern whose mass reaches P. Four-way steps:
-// three probes, three independent reductions. The probed sets are nested and
-// summed in the same order, so the computed masses are ordered like the exact
-// ones and the decisions are consistent. Theta is a list value: once a single
-// entry remains in [lo, hi), it is theta. Once at most 64 entries remain in
-// the bracket, the mass at or above hi is fixed (B) and those entries move to
-// one per lane (through `scr`, 64 floats of LDS the list wave owns): each
-// later probe is B plus one compare per lane instead of a pass over the run.
+// Theta from the list (list wave; n entries): the largest value whose mass
+// reaches P, which lies in [lo, hi) (bit patterns). Four-way steps (three
+// probes, three independent reductions; the probed sets are nested and summed
+// in the same order, so the computed masses are ordered like the exact ones)
+// until at most 64 entries lie in the bracket. The mass at or above hi is then
+// fixed, those entries move to one per lane (through `scr`), and each lane
+// takes the mass at or above its own entry: the largest entry whose mass
+// reaches P is theta, with no further search.
 template <int RUN>
-__device__ __forceinline__ float list_theta(const float (&w)[RUN], float c, float P, float* scr) {
+__device__ __forceinline__ float list_theta(const float (&w)[RUN], uint32_t lo, uint32_t hi,
+                                            float P, float* scr) {
   const int lane = threadIdx.x & 63;
-  // invariant: S(lo) >= P > S(hi); lo, hi and the decisions are wave-uniform
-  uint32_t lo = __float_as_uint(c), hi = 0x3f800001u;  // nothing is above 1
-  while (hi - lo > 1) {
+  int n2;
+  for (;;) {
     int inside = 0;
-    float last = 0.f;
 #pragma unroll
     for (int q = 0; q < RUN; ++q) {
       const uint32_t b = __float_as_uint(w[q]);
-      const bool in = b >= lo && b < hi;
-      inside += in ? 1 : 0;
-      last = in ? w[q] : last;
+      inside += b >= lo && b < hi ? 1 : 0;
     }
-    const unsigned long long any = __ballot(inside > 0);
-    if (__builtin_popcountll(any) == 1 && __ballot(inside > 1) == 0) {
-      const float v = __builtin_bit_cast(
-          float, __builtin_amdgcn_readlane(__float_as_int(last), __builtin_ctzll(any)));
-      return v;
-    }
-    if (RUN > 1 && wave_sum(inside) <= 64) break;
-    if (hi - lo > 3) {
-      const uint32_t st = (hi - lo) >> 2;
-      const uint32_t m1 = lo + st, m2 = m1 + st, m3 = m2 + st;
-      float p1 = 0.f, p2 = 0.f, p3 = 0.f;
+    n2 = wave_sum(inside);
+    if (RUN == 1 || n2 <= 64 || hi - lo <= 3) break;
+    const uint32_t st = (hi - lo) >> 2;
+    const uint32_t m1 = lo + st, m2 = m1 + st, m3 = m2 + st;
+    float p1 = 0.f, p2 = 0.f, p3 = 0.f;
 #pragma unroll
-      for (int q = 0; q < RUN; ++q) {
-        const uint32_t b = __float_as_uint(w[q]);
-        p1 += b >= m1 ? w[q] : 0.f;
-        p2 += b >= m2 ? w[q] : 0.f;
-        p3 += b >= m3 ? w[q] : 0.f;
-      }
-      const int g1 = __builtin_amdgcn_readfirstlane(wave_sum(p1) >= P ? 1 : 0);
-      const int g2 = __builtin_amdgcn_readfirstlane(wave_sum(p2) >= P ? 1 : 0);
-      const int g3 = __builtin_amdgcn_readfirstlane(wave_sum(p3) >= P ? 1 : 0);
-      if (g3) {
-        lo = m3;
-      } else if (g2) {
-        lo = m2;
-        hi = m3;
-      } else if (g1) {
-        lo = m1;
-        hi = m2;
-      } else {
-        hi = m1;
-      }
+    for (int q = 0; q < RUN; ++q) {
+      const uint32_t b = __float_as_uint(w[q]);
+      p1 += b >= m1 ? w[q] : 0.f;
+      p2 += b >= m2 ? w[q] : 0.f;
+      p3 += b >= m3 ? w[q] : 0.f;
+    }
+    const int g1 = __builtin_amdgcn_readfirstlane(wave_sum(p1) >= P ? 1 : 0);
+    const int g2 = __builtin_amdgcn_readfirstlane(wave_sum(p2) >= P ? 1 : 0);
+    const int g3 = __builtin_amdgcn_readfirstlane(wave_sum(p3) >= P ? 1 : 0);
+    if (g3) {
+      lo = m3;
+    } else if (g2) {
+      lo = m2;
+      hi = m3;
+    } else if (g1) {
+      lo = m1;
+      hi = m2;
     } else {
-      const uint32_t mid = lo + (hi - lo) / 2;
-      float part = 0.f;
-#pragma unroll
-      for (int q = 0; q < RUN; ++q) part += __float_as_uint(w[q]) >= mid ? w[q] : 0.f;
-      if (__builtin_amdgcn_readfirstlane(wave_sum(part) >= P ? 1 : 0))
-        lo = mid;
-      else
-        hi = mid;
+      hi = m1;
     }
   }
-  if (hi - lo <= 1) return __uint_as_float(lo);
-  // at most 64 entries in [lo, hi): B = the mass at or above hi, and the
-  // bracket's entries one per lane (in run order)
+  if (n2 == 0) return __uint_as_float(lo);  // rounding: the entries at or above hi are kept
+  if (n2 > 64) {  // three or fewer bit patterns with more than 64 entries (ties): one probe each
+    for (uint32_t b = hi - 1; b > lo; --b) {
+      float p = 0.f;
+#pragma unroll
+      for (int q = 0; q < RUN; ++q) p += __float_as_uint(w[q]) >= b ? w[q] : 0.f;
+      if (__builtin_amdgcn_readfirstlane(wave_sum(p) >= P ? 1 : 0)) return __uint_as_float(b);
+    }
+    return __uint_as_float(lo);
+  }
   float base = 0.f;
   int cnt = 0;
 #pragma unroll
@@ -593,57 +541,37 @@ __device__ __forceinline__ float list_theta(const float (&w)[RUN], float c, floa
     cnt += (b >= lo && b < hi) ? 1 : 0;
   }
   const float B = wave_sum(base);
-  const int incl = wave_incl_scan(cnt);
-  const int n2 = __builtin_amdgcn_readlane(incl, 63);
-  int pos = incl - cnt;
+  int pos = wave_incl_scan(cnt) - cnt;
 #pragma unroll
   for (int q = 0; q < RUN; ++q) {
     const uint32_t b = __float_as_uint(w[q]);
     if (b >= lo && b < hi) scr[pos++] = w[q];
   }
   const float x = lane < n2 ? scr[lane] : 0.f;
-  const uint32_t bx = __float_as_uint(x);
-  while (hi - lo > 1) {
-    const unsigned long long in = __ballot(lane < n2 && bx >= lo && bx < hi);
-    if (__builtin_popcountll(in) == 1)
-      return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__float_as_int(x), __builtin_ctzll(in)));
-    if (hi - lo > 3) {
-      const uint32_t st = (hi - lo) >> 2;
-      const uint32_t m1 = lo + st, m2 = m1 + st, m3 = m2 + st;
-      const int g1 = __builtin_amdgcn_readfirstlane(B + wave_sum(bx >= m1 ? x : 0.f) >= P ? 1 : 0);
-      const int g2 = __builtin_amdgcn_readfirstlane(B + wave_sum(bx >= m2 ? x : 0.f) >= P ? 1 : 0);
-      const int g3 = __builtin_amdgcn_readfirstlane(B + wave_sum(bx >= m3 ? x : 0.f) >= P ? 1 : 0);
-      if (g3) {
-        lo = m3;
-      } else if (g2) {
-        lo = m2;
-        hi = m3;
-      } else if (g1) {
-        lo = m1;
-        hi = m2;
-      } else {
-        hi = m1;
-      }
-    } else {
-      const uint32_t mid = lo + (hi - lo) / 2;
-      if (__builtin_amdgcn_readfirstlane(B + wave_sum(bx >= mid ? x : 0.f) >= P ? 1 : 0))
-        lo = mid;
-      else
-        hi = mid;
+  float part[4] = {B, 0.f, 0.f, 0.f};  // (entries n2 .. 63 are 0 and add nothing)
+  for (int k = 0; k < n2; k += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float y = lane_read(x, k + q);
+      part[q] += y >= x ? y : 0.f;
     }
   }
-  return __uint_as_float(lo);
+  const float mass = (part[0] + part[1]) + (part[2] + part[3]);
+  // (the smallest entry's mass reaches P up to rounding; it is taken if none does)
+  const float smallest = -wave_max(lane < n2 ? -x : -INFINITY);
+  const float best = wave_max(lane < n2 && mass >= P ? x : 0.f);
+  return best > 0.f ? best : smallest;
 }
 
-// Completes a row's distribution from its final list (list wave): theta, the
+// Completes a row's distribution from its list (list wave; theta in [lo, hi)): theta, the
 // tie cut and the kept mass. `kw` receives the kept weights of the lane's run.
 template <int RUN>
-__device__ __forceinline__ void run_dist(RowShared& sh, int n, float c, float P, int V,
-                                         RowDist& d, float (&kw)[RUN]) {
+__device__ __forceinline__ void run_dist(RowShared& sh, int n, uint32_t lo, uint32_t hi, float P,
+                                         int V, RowDist& d, float (&kw)[RUN]) {
   const int lane = threadIdx.x & 63;
   float w[RUN];
   load_run<RUN>(sh, n, w);
-  const float th = list_theta<RUN>(w, c, P, sh.bw);  // the first list is spent by now
+  const float th = list_theta<RUN>(w, lo, hi, P, sh.scr);
   d.theta = th;
   float above = 0.f;
   int ties = 0;
@@ -681,165 +609,179 @@ __device__ __forceinline__ void run_dist(RowShared& sh, int n, float c, float P,
   d.kept = wave_sum(kp);
 }
 
-// Mass and count of the weights at or above t (block-wide).
-template <int EPT>
-__device__ __forceinline__ void mass_at(const float* e, float t, float& F, int& n, RowShared& sh) {
-  F = 0.f;
-  n = 0;  // per wave: the same in every lane
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const bool in = e[i] >= t;
-    F += in ? e[i] : 0.f;
-    n += __builtin_popcountll(__ballot(in));
-  }
-  block_sum2w(F, n, sh);
+__device__ __forceinline__ unsigned long long fixed_mass(float e) {
+  return (unsigned long long)(e * 17592186044416.f);  // 2^44; a row's sum stays below 2^60
 }
 
-// Mass and count of the list entries w[] >= t held by the threads (block-wide).
-__device__ __forceinline__ void list_mass(const float (&w)[4], float t, float& F, int& n,
-                                          RowShared& sh) {
-  F = 0.f;
-  n = 0;
+// The first bin, from bin 0 on, at which `above` plus the masses up to it reach
+// P (2^-44 units); `above` becomes the mass before that bin. -1 if none does.
+// Every wave runs it on its own.
+template <int NB>
+__device__ __forceinline__ int pick_bin(const unsigned long long* hist, double P, double& above) {
+  constexpr int PER = NB / 64;
+  const int lane = threadIdx.x & 63;
+  double h[PER];
+  double run = 0.0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    F += w[q] >= t ? w[q] : 0.f;
-    n += w[q] >= t ? 1 : 0;
+  for (int q = 0; q < PER; ++q) {
+    h[q] = (double)hist[lane * PER + q];
+    run += h[q];
   }
-  block_sum2(F, n, sh);
-}
-
-// Loads a row and computes its sampling distribution. `e` receives the
-// thread's exp weights exp(l / T - max) (0 beyond V). With a nucleus and a
-// small candidate set the candidates (weights >= `c`) are left in the LDS
-// list and their number is returned: then only m and total are set in d, and
-// the list wave completes it (run_dist). Otherwise the whole distribution is
-// in d for every thread and -1 is returned.
-template <int EPT>
-__device__ __forceinline__ int row_dist(const float* row, int V, float inv_temp, float top_p,
-                                        float* e, RowShared& sh, RowDist& d, float& c, float& P) {
-  load_row<EPT>(row, V, e);
-  const int nv = elems_in_row<EPT>(V);
-  float mx = -INFINITY;
+  const double incl = wave_incl_scan(run);
+  const unsigned long long hit = __ballot(above + incl >= P);
+  if (!hit) return -1;
+  const int L = __builtin_ctzll(hit);
+  double before = above + incl - run;
+  int bin = PER - 1;
+  bool found = false;
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    e[i] = i < nv ? scaled_logit(e[i], inv_temp) : -INFINITY;
-    mx = fmaxf(mx, e[i]);
-  }
-  d.m = block_max(mx, sh);
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    e[i] = e[i] == -INFINITY ? 0.f : weight_of(e[i], d.m);
-    s += e[i];
-  }
-  d.total = block_sum(s, sh);
-  d.theta = 0.f;
-  d.tie_cut = V;
-  d.kept = d.total;
-  if (!(top_p < 1.f)) return -1;
-  P = top_p * d.total;
-  c = (1.f - top_p) * d.total / (float)V;
-  bool ok = c > 0.f;
-  if (ok) {
-    const float c0 = c;
-    bool fits;
-    compact_regions<EPT>([&](int i) { return e[i] >= c0; }, [&](int i) { return e[i]; }, sh,
-                         fits);
-    if (fits) {
-      // the bound rounds run on the first list: the thread holds entries 4 lane
-      // .. 4 lane + 3 of its wave's region, so thread order is index order
-      const int lane = threadIdx.x & 63;
-      const int wave = threadIdx.x >> 6;
-      const int nw = sh.wcnt[wave];
-      float w[4];
-      int ix[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int j = 4 * lane + q;
-        w[q] = j < nw ? sh.bw[wave * kRegion + j] : 0.f;
-        ix[q] = sh.bi[wave * kRegion + j];
-      }
-      float F;
-      int n;
-      list_mass(w, c, F, n, sh);
-      ok = F >= P;
-      for (int r = 0; ok && r < kBoundRounds && n > kSmallCand; ++r) {
-        const float t = (F - P) / (float)n;
-        if (!(t > c)) break;
-        float F2;
-        int n2;
-        list_mass(w, t, F2, n2, sh);
-        if (!(F2 >= P)) break;
-        c = t;
-        F = F2;
-        n = n2;
-      }
-      if (ok && n <= kMaxCand) {  // stable compaction of the weights >= c into the final list
-        int cnt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cnt += w[q] >= c ? 1 : 0;
-        const int incl = wave_incl_scan(cnt);
-        if (lane == 63) sh.ired[wave] = incl;
-        __syncthreads();
-        int pos = incl - cnt;
-#pragma unroll
-        for (int k = 0; k < kRowWaves; ++k) pos += k < wave ? sh.ired[k] : 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (w[q] >= c) {
-            sh.cw[cand_slot(pos)] = w[q];
-            sh.ci[cand_slot(pos)] = ix[q];
-            ++pos;
-          }
-        __syncthreads();
-        return n;
-      }
-    } else {
-      // a large first list: the rounds run over the thread's row elements
-      float F;
-      int n;
-      mass_at<EPT>(e, c, F, n, sh);
-      ok = F >= P;
-      for (int r = 0; ok && r < kBoundRounds && n > kSmallCand; ++r) {
-        const float t = (F - P) / (float)n;
-        if (!(t > c)) break;
-        float F2;
-        int n2;
-        mass_at<EPT>(e, t, F2, n2, sh);
-        if (!(F2 >= P)) break;
-        c = t;
-        F = F2;
-        n = n2;
-      }
-      if (ok && n <= kMaxCand) {
-        const float cc = c;
-        return compact_row<EPT, kMaxCand, true>([&](int i) { return e[i] >= cc; },
-                                                [&](int i) { return e[i]; }, sh.cw, sh.ci, sh);
+  for (int q = 0; q < PER; ++q) {
+    if (!found) {
+      if (q == PER - 1 || before + h[q] >= P) {
+        bin = q;
+        found = true;
+      } else {
+        before += h[q];
       }
     }
   }
-  // whole-row search: largest bit pattern b with sum(e >= b) >= P
-  uint32_t lo = 0, hi = 0x3f800001u;  // sum(e >= 0) = total >= P; nothing is above 1
-  if (ok) lo = __float_as_uint(c);  // S(c) >= P was checked
-  while (hi - lo > 1) {
-    const uint32_t mid = lo + (hi - lo) / 2;
-    float part = 0.f;
+  above = lane_read(before, L);
+  return L * PER + __builtin_amdgcn_readlane(bin, L);
+}
+
+// Loads a row and computes its sampling distribution. `e` receives the
+// thread's exp weights exp(l / T - max) (0 beyond V). With a nucleus that fits
+// the list, the weights of bit patterns >= `lo` are left there and their number
+// is returned: then only m and total are set in d, and the list wave completes
+// it (run_dist; theta lies in [lo, hi)). Otherwise the whole distribution is in
+// d for every thread and -1 is returned.
+template <int EPT>
+__device__ __forceinline__ int row_dist(const float* row, int V, float inv_temp, float top_p,
+                                        float* e, RowShared& sh, RowDist& d, uint32_t& lo,
+                                        uint32_t& hi, float& P) {
+  constexpr int kRun = EPT / kGroups;
+  load_row<EPT>(row, V, e);
+  if (threadIdx.x < kMaxBins) sh.maxhist[threadIdx.x] = 0;
+  const int nv = elems_in_row<EPT>(V);
+  float mx[kGroups];
 #pragma unroll
-    for (int i = 0; i < EPT; ++i) part += __float_as_uint(e[i]) >= mid ? e[i] : 0.f;
-    if (block_sum(part, sh) >= P)
-      lo = mid;
-    else
-      hi = mid;
+  for (int g = 0; g < kGroups; ++g) {
+    mx[g] = -INFINITY;
+#pragma unroll
+    for (int i = g * kRun; i < (g + 1) * kRun; ++i) {
+      e[i] = i < nv ? scaled_logit(e[i], inv_temp) : -INFINITY;
+      mx[g] = fmaxf(mx[g], e[i]);
+    }
+  }
+  d.m = block_max_once(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])), sh.rmax);
+  const float m = d.m == -INFINITY ? 0.f : d.m;  // a row of -inf: every weight 0
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    e[i] = weight_of(e[i], m);
+    s += e[i];
+  }
+  const bool nucleus = top_p < 1.f;
+  if (nucleus) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      const float w = weight_of(mx[g], m);  // the run's largest weight
+      const int bin = (int)(kOne >> kMaxShift) - (int)(__float_as_uint(w) >> kMaxShift);
+      if (bin >= 0 && bin < kMaxBins - 1) atomicAdd(&sh.maxhist[bin], (unsigned)(w * 32768.f));
+    }
+  }
+  d.total = block_sum_once(s, sh.rsum);
+  d.theta = 0.f;
+  d.tie_cut = V;
+  d.kept = d.total;
+  if (!nucleus) return -1;
+  P = top_p * d.total;
+  lo = 0;
+  hi = kOne + 1;  // nothing is above 1
+  {
+    // rounded down, the masses never overstate the maxima's
+    const unsigned incl = wave_incl_scan((int)sh.maxhist[threadIdx.x & 63]);
+    const unsigned long long hit = __ballot((float)incl >= P * 32768.f * 1.000001f);
+    if (hit && d.total > 0.f) {
+      const uint32_t c = ((kOne >> kMaxShift) - (uint32_t)__builtin_ctzll(hit)) << kMaxShift;
+      const int n = compact_row<EPT>(e, c, sh);
+      if (n <= kMaxCand) {
+        lo = c;
+        return n;
+      }
+    }
+  }
+  // radix selection over all weights >= c0 (at most 1)
+  __syncthreads();
+  for (int b = threadIdx.x; b < kBins; b += kRowThreads) sh.hist[b] = 0;
+  __syncthreads();
+  const float c0 = (1.f - top_p) * d.total / (float)V;
+  pass_fence<EPT>(e);
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const bool in = e[i] >= c0 && e[i] > 0.f;
+    if (__ballot(in) == 0) continue;
+    if (in) {
+      const int bin = (int)(kOne >> kTopShift) - (int)(__float_as_uint(e[i]) >> kTopShift);
+      atomicAdd(&sh.hist[bin < kBins ? bin : kBins - 1], fixed_mass(e[i]));
+    }
+  }
+  __syncthreads();
+  const double Pd = (double)P * 17592186044416.0;
+  double above = 0.0;
+  const int bin = pick_bin<kBins>(sh.hist, Pd, above);
+  if (bin >= 0 && bin < kBins - 1 && d.total > 0.f) {
+    lo = ((kOne >> kTopShift) - (uint32_t)bin) << kTopShift;
+    if (bin > 0) hi = lo + (1u << kTopShift);
+    const int n = compact_row<EPT>(e, lo, sh);
+    if (n <= kMaxCand) return n;
+    // the nucleus overflows the list: the bin's remaining bits, 8 + 8 + 4 at a time
+#pragma unroll 1
+    for (int shift = kTopShift; shift > 0;) {
+      const int bits = shift >= 8 ? 8 : shift;
+      const int sh2 = shift - bits;
+      __syncthreads();  // the previous level's histogram has been read
+      if (threadIdx.x < 256) sh.hist[threadIdx.x] = 0;
+      __syncthreads();
+      pass_fence<EPT>(e);
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) {
+        const uint32_t b = __float_as_uint(e[i]);
+        const bool in = b >= lo && b < hi;
+        if (__ballot(in) == 0) continue;
+        if (in) atomicAdd(&sh.hist[((1 << bits) - 1) - (int)((b - lo) >> sh2)], fixed_mass(e[i]));
+      }
+      __syncthreads();
+      const int k = pick_bin<256>(sh.hist, Pd, above);
+      // (the masses of the level add up to the bin's, so some digit reaches P)
+      lo += (uint32_t)(((1 << bits) - 1) - (k < 0 ? (1 << bits) - 1 : k)) << sh2;
+      hi = lo + (1u << sh2);
+      shift = sh2;
+    }
+  } else {
+    // no weight (or NaN), or rounding left the histogram's mass below P (top_p
+    // within an ulp of 1): the largest bit pattern b with sum(e >= b) >= P;
+    // sum(e >= 0) = total does
+    while (hi - lo > 1) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      float part = 0.f;
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) part += __float_as_uint(e[i]) >= mid ? e[i] : 0.f;
+      if (block_sum(part, sh) >= P)
+        lo = mid;
+      else
+        hi = mid;
+    }
   }
   d.theta = __uint_as_float(lo);
-  float above = 0.f;
+  float above_f = 0.f;
   int ties = 0;
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    above += e[i] > d.theta ? e[i] : 0.f;
+    above_f += e[i] > d.theta ? e[i] : 0.f;
     ties += (e[i] == d.theta && e[i] > 0.f) ? 1 : 0;
   }
-  const float mass_above = block_sum(above, sh);
+  const float mass_above = block_sum(above_f, sh);
   const int n_tie = block_count(ties, sh);
   int k = n_tie;
   if (n_tie > 1 && d.theta > 0.f) {
@@ -902,18 +844,23 @@ __device__ __forceinline__ int row_argmax(const float* row, int V, RowShared& sh
   return bi;
 }
 
-// The distribution from the final list (every thread calls it; only wave 0
-// works, the other waves return -2 at once), then (with u >= 0) a draw;
+// The distribution from the list (list wave), then (with u >= 0) a draw;
 // returns the drawn token (or -1 without a draw).
 template <int RUN>
-__device__ __forceinline__ int list_finish(RowShared& sh, int n, float c, float P, int V,
-                                           float u, RowDist& d) {
-  if (threadIdx.x >= 64) return -2;
+__device__ __forceinline__ int list_finish_run(RowShared& sh, int n, uint32_t lo, uint32_t hi,
+                                               float P, int V, float u, RowDist& d) {
   float kw[RUN];
-  run_dist<RUN>(sh, n, c, P, V, d, kw);
+  run_dist<RUN>(sh, n, lo, hi, P, V, d, kw);
   if (u < 0.f) return -1;
   const int j = run_draw<RUN>(kw, u * d.kept);
   return sh.ci[cand_slot(j)];
+}
+// One, 4 or 16 entries per lane.
+__device__ __forceinline__ int list_finish(RowShared& sh, int n, uint32_t lo, uint32_t hi, float P,
+                                           int V, float u, RowDist& d) {
+  return n <= 64           ? list_finish_run<1>(sh, n, lo, hi, P, V, u, d)
+         : n <= kSmallCand ? list_finish_run<4>(sh, n, lo, hi, P, V, u, d)
+                           : list_finish_run<kRunMax>(sh, n, lo, hi, P, V, u, d);
 }
 
 template <int EPT>
@@ -927,12 +874,12 @@ __global__ __launch_bounds__(kRowThreads) void sample_kernel(SampleArgs a) {
   } else {
     float e[EPT];
     RowDist d;
-    float c = 0.f, P = 0.f;
-    const int n = row_dist<EPT>(row, (int)a.V, a.inv_temp, a.top_p, e, sh, d, c, P);
+    uint32_t lo = 0, hi = 0;
+    float P = 0.f;
+    const int n = row_dist<EPT>(row, (int)a.V, a.inv_temp, a.top_p, e, sh, d, lo, hi, P);
     if (n >= 0) {
-      tok = n <= kSmallCand ? list_finish<4>(sh, n, c, P, (int)a.V, a.u[r], d)
-                            : list_finish<kRunMax>(sh, n, c, P, (int)a.V, a.u[r], d);
       if (threadIdx.x >= 64) return;
+      tok = list_finish(sh, n, lo, hi, P, (int)a.V, a.u[r], d);
     } else {
       tok = row_draw<EPT>(e, d, a.u[r], sh);
     }
@@ -950,14 +897,12 @@ __global__ __launch_bounds__(kRowThreads) void row_params_kernel(RowParamArgs a)
   const float* row = r < a.rows0 ? a.logits0 + r * a.V : a.logits1 + (r - a.rows0) * a.V;
   float e[EPT];
   RowDist d;
-  float c = 0.f, P = 0.f;
-  const int n = row_dist<EPT>(row, (int)a.V, a.inv_temp, a.top_p, e, sh, d, c, P);
+  uint32_t lo = 0, hi = 0;
+  float P = 0.f;
+  const int n = row_dist<EPT>(row, (int)a.V, a.inv_temp, a.top_p, e, sh, d, lo, hi, P);
   if (n >= 0) {
-    if (n <= kSmallCand)
-      list_finish<4>(sh, n, c, P, (int)a.V, -1.f, d);
-    else
-      list_finish<kRunMax>(sh, n, c, P, (int)a.V, -1.f, d);
     if (threadIdx.x >= 64) return;
+    list_finish(sh, n, lo, hi, P, (int)a.V, -1.f, d);
   }
   if (threadIdx.x == 0) a.params[r] = d;
 }
@@ -1011,8 +956,7 @@ __device__ __forceinline__ int compact_kept(const float* prow, int V, float it, 
     const float e = exp_weight(w[i], it, dp);
     w[i] = i < nv && kept_w(e, v0 + 64 * i, dp) ? e : 0.f;
   }
-  return compact_row<EPT, kMaxCand, true>([&](int i) { return w[i] > 0.f; },
-                                          [&](int i) { return w[i]; }, sh.cw, sh.ci, sh);
+  return compact_row<EPT>(w, 1u, sh);  // every positive weight
 }
 
 // List wave: a draw from p's kept list (n entries) with uniform u; with a
@@ -1043,7 +987,10 @@ __device__ __forceinline__ int list_residual_draw(const RowShared& sh, int n, co
 // Verification: one block per sequence. Rows' parameters come from
 // row_params_kernel; weights are recomputed from the logits as needed (the
 // rows stay in L2). The draw after a rejection (or after the last draft) runs
-// over the verifier row's kept tokens, which hold all of max(0, p - q).
+// over the verifier row's kept tokens, which hold all of max(0, p - q). Bound by
+// latency: 32 us per launch (102 sequences of 6 drafts at V = 49,152) with the
+// drafts tested one after the other and two passes over the row for the kept
+// tokens, 20 us with the tests side by side and one pass.
 template <int EPT, bool GREEDY>
 __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
   __shared__ RowShared sh;
@@ -1053,33 +1000,48 @@ __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
   const float it = a.inv_temp;
   int k = 0;
   int next = 0;
+  if (GREEDY) {
 #pragma nounroll
-  for (; k < G; ++k) {
-    const int x = a.draft_tokens[(int64_t)k * a.batch + b];
-    const float* trow = a.target_logits + (b * (G + 1) + k) * a.V;
-    if (GREEDY) {
-      const int best = row_argmax<EPT>(trow, V, sh);
-      if (best != x) {
-        next = best;
-        break;
-      }
-      continue;
+    for (; k < G; ++k) {
+      next = row_argmax<EPT>(a.target_logits + (b * (G + 1) + k) * a.V, V, sh);
+      if (next != a.draft_tokens[(int64_t)k * a.batch + b]) break;
     }
+  } else {
+    // The acceptance tests do not depend on each other: one lane per draft, so
+    // that a sequence waits for one chain of loads (token, logits) rather than
+    // one per kept draft. Every wave does it for itself.
+#pragma nounroll
+    for (int k0 = 0; k0 < G; k0 += 64) {
+      const int kl = k0 + (int)(threadIdx.x & 63);
+      bool rejected = false;
+      if (kl < G) {
+        const int64_t at = (int64_t)kl * a.batch + b;
+        const int x = a.draft_tokens[at];
+        const RowDist dq = a.dparams[at];
+        const RowDist dp = a.tparams[b * (G + 1) + kl];
+        const bool in = x >= 0 && x < V;
+        const float qx = in ? prob_at(a.draft_logits + at * a.V, x, it, dq) : 0.f;
+        const float px = in ? prob_at(a.target_logits + (b * (G + 1) + kl) * a.V, x, it, dp) : 0.f;
+        rejected = !(a.u_accept[at] * qx < px);
+      }
+      const unsigned long long m = __ballot(rejected);
+      k = k0 + (m ? __builtin_ctzll(m) : 64);
+      if (m) break;
+    }
+    k = k < G ? k : G;
+  }
+  if (!GREEDY && k < G) {
+    const float* trow = a.target_logits + (b * (G + 1) + k) * a.V;
     const float* drow = a.draft_logits + ((int64_t)k * a.batch + b) * a.V;
     const RowDist dq = a.dparams[(int64_t)k * a.batch + b];
     const RowDist dp = a.tparams[b * (G + 1) + k];
-    const bool in = x >= 0 && x < V;
-    const float qx = in ? prob_at(drow, x, it, dq) : 0.f;
-    const float px = in ? prob_at(trow, x, it, dp) : 0.f;
-    if (a.u_accept[(int64_t)k * a.batch + b] * qx < px) continue;
     // rejected: draw from max(0, p - q)
     const int n = compact_kept<EPT>(trow, V, it, dp, sh);
     if (n <= kMaxCand) {
       if (threadIdx.x >= 64) return;
       next = n <= kSmallCand ? list_residual_draw<4>(sh, n, dp, drow, dq, it, a.u_sample[b])
-                         : list_residual_draw<kRunMax>(sh, n, dp, drow, dq, it, a.u_sample[b]);
-      break;
-    }
+                             : list_residual_draw<kRunMax>(sh, n, dp, drow, dq, it, a.u_sample[b]);
+    } else {
     auto res = [&](int i) {
       const int v = elem_v<EPT>(i);
       if (v >= V) return 0.f;
@@ -1105,7 +1067,7 @@ __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
       // distributions and they coincide, so the draw is from the verifier's
       next = draw_kept<EPT>(trow, V, it, dp, a.u_sample[b], sh);
     }
-    break;
+    }
   }
   if (k == G) {  // every draft kept: one more token from the verifier
     const float* trow = a.target_logits + (b * (G + 1) + G) * a.V;

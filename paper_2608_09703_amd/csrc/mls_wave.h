@@ -54,6 +54,15 @@ __device__ __forceinline__ float wave_sum(float v) {
   return (lane_read(v, 0) + lane_read(v, 16)) + (lane_read(v, 32) + lane_read(v, 48));
 }
 
+// Sum over the 16 lanes of each lane row.
+__device__ __forceinline__ float row16_sum(float v) {
+  v += dpp_move<dppc::kXor1>(v, 0.f);
+  v += dpp_move<dppc::kXor2>(v, 0.f);
+  v += dpp_move<dppc::kHalfMirror>(v, 0.f);
+  v += dpp_move<dppc::kMirror>(v, 0.f);
+  return v;
+}
+
 __device__ __forceinline__ int wave_sum(int v) {
   v += dpp_move<dppc::kXor1>(v, 0);
   v += dpp_move<dppc::kXor2>(v, 0);
@@ -116,6 +125,40 @@ __device__ __forceinline__ float wave_incl_scan(float v) {
   const float t01 = t0 + t1;
   const float off = row == 0 ? 0.f : row == 1 ? t0 : row == 2 ? t01 : t01 + t2;
   return row == 0 ? v : v + off;
+}
+
+template <int Ctrl>
+__device__ __forceinline__ double dpp_move(double v) {  // 0 past the row
+  const long long b = __double_as_longlong(v);
+  const int lo = dpp_move<Ctrl>((int)b, 0);
+  const int hi = dpp_move<Ctrl>((int)(b >> 32), 0);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_read(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_incl_scan(double v) {
+  v += dpp_move<dppc::kShr + 1>(v);
+  v += dpp_move<dppc::kShr + 2>(v);
+  v += dpp_move<dppc::kShr + 4>(v);
+  v += dpp_move<dppc::kShr + 8>(v);
+  const int row = (threadIdx.x & 63) >> 4;
+  const double t0 = lane_read(v, 15);
+  const double t01 = t0 + lane_read(v, 31);
+  const double t012 = t01 + lane_read(v, 47);
+  return v + (row == 0 ? 0.0 : row == 1 ? t0 : row == 2 ? t01 : t012);
+}
+
+// Inclusive prefix sum within each 16-lane row.
+__device__ __forceinline__ int row16_incl_scan(int v) {
+  v += dpp_move<dppc::kShr + 1>(v, 0);
+  v += dpp_move<dppc::kShr + 2>(v, 0);
+  v += dpp_move<dppc::kShr + 4>(v, 0);
+  v += dpp_move<dppc::kShr + 8>(v, 0);
+  return v;
 }
 
 __device__ __forceinline__ int wave_incl_scan(int v) {
