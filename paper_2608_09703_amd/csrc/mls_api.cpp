@@ -87,6 +87,8 @@ constexpr int64_t kMinChunks = 4;                 // the default plan never hold
 constexpr int64_t kRecordBudget = 1ll << 30;      // forward partial records of one token chunk
 constexpr int64_t kLogitSlabBudget = 16ll << 30;  // stored logits of one token chunk (all sub-models)
 constexpr int64_t kPanelMax = (1ll << 32) - 1;    // bytes one wide-GEMM operand may span
+constexpr int64_t kCus = 256;                     // compute units of the part
+constexpr int64_t kMaxSplits = 16;                // K parts of a grad_h product
 
 struct Plan {
   int M = 0;
@@ -124,6 +126,11 @@ struct Plan {
   // backward workspace (off_ghp: fp32 partial sums of a bf16 grad_h over vocabulary chunks)
   bool grad_h_bf16 = false;
   size_t off_slab = 0, off_slabT = 0, off_hT = 0, off_WT = 0, off_ghp = 0, bwd_bytes = 0;
+  // K parts of the wide grad_h products (1: none), each of *_ks elements of K,
+  // with fp32 partial outputs at off_ghp / fb_off_ghp
+  int bwd_splits = 1, fb_splits = 1;
+  int64_t bwd_ks = 0, fb_ks = 0;
+  size_t fb_off_ghp = 0;
   // diagnostics workspace (vocabulary segments of the pairwise pass)
   int n_vt_diag = 0, n_tt_diag = 0;
   int m_diag = 0;  // sub-models per diagnostics pass (at most kMaxDiagModels)
@@ -132,6 +139,62 @@ struct Plan {
   size_t stats_bytes = 0;
   size_t header_off = 0;
 };
+
+// Time, in the unit of the costs, that n1 tiles of cost c1 followed by n2 tiles
+// of cost c2 take when every CU takes its next tile as it becomes free.
+int64_t launch_span(int64_t n1, int64_t c1, int64_t n2, int64_t c2) {
+  const int64_t q = n1 / kCus, r = n1 % kCus;  // r CUs take one more of the first kind
+  int64_t lo = q * c1 + (r ? c1 : 0), hi = lo + (n2 / kCus + 1) * c2;
+  while (lo < hi) {
+    const int64_t t = (lo + hi) / 2;
+    const int64_t room = r * (std::max<int64_t>(0, t - (q + 1) * c1) / c2) +
+                         (kCus - r) * (std::max<int64_t>(0, t - q * c1) / c2);
+    if (room >= n2)
+      hi = t;
+    else
+      lo = t + 1;
+  }
+  return lo;
+}
+
+// K parts of the grad_h products of one launch of the wide gradient GEMM over
+// `rows` tokens and `vrows` vocabulary rows, and the K extent of a part. A
+// grad_h tile runs over all of vrows, a grad_W tile over the tokens only, so
+// with few tokens the launch has few, long grad_h tiles and lasts as long as one
+// of them while most CUs are done. K is cut into as many parts (at most
+// kMaxSplits) as give the shortest launch by a count of K-tiles per CU, a tile's
+// prologue and output counted as 3 and the sum over the parts at 5 TB/s; not
+// for less than 4 %. Forward + backward at T = 512, widths 1,024 / 2,048 /
+// 3,072, V = 50,304: 3,268 -> 1,768 us; T = 1,024, widths 512 / 1,024, V =
+// 32,000: 1,502 -> 530 us. With 4,096 tokens of the headline shape one part
+// remains the shortest.
+void grad_h_parts(const mls_problem* p, int64_t rows, int64_t vrows, int* splits, int64_t* ksplit) {
+  constexpr int64_t kTileCost = 3;       // K-tiles
+  constexpr int64_t kTileBytes = 8 << 20;  // bytes at 5 TB/s in a K-tile's 1.7 us
+  const int64_t bm = gemm_tile_rows(true), bn = gemm_tile_cols(true), bk = gemm_wide_k_tile();
+  const int64_t nk = (vrows + bk - 1) / bk, nkw = (rows + bk - 1) / bk;
+  int64_t cols = 0, sumd = 0;
+  for (int i = 0; i < p->M; ++i) {
+    cols += (p->d[i] + bn - 1) / bn;
+    sumd += p->d[i];
+  }
+  const int64_t n1 = (rows + bm - 1) / bm * cols, n2 = (vrows + bm - 1) / bm * cols;
+  *splits = 1;
+  *ksplit = nk * bk;
+  int64_t best = launch_span(n1, nk + kTileCost, n2, nkw + kTileCost);
+  best -= best / 25;
+  for (int64_t want = 2; want <= kMaxSplits && nk / want >= 8; ++want) {
+    const int64_t per = (nk + want - 1) / want;
+    const int64_t s = (nk + per - 1) / per;
+    const int64_t t = launch_span(n1 * s, per + kTileCost, n2, nkw + kTileCost) +
+                      2 * s * rows * sumd * 4 / kTileBytes;
+    if (t < best) {
+      best = t;
+      *splits = (int)s;
+      *ksplit = per * bk;
+    }
+  }
+}
 
 mls_status validate(const mls_problem* p) {
   if (!p) return fail(MLS_INVALID_ARG, "problem is NULL");
@@ -235,9 +298,11 @@ void make_plan(const mls_problem* p, Plan& pl) {
     pl.off_WT = off;
     off = align256(off + (size_t)pl.sumd * pl.Vc * pl.es);
   }
-  if (pl.grad_h_bf16 && pl.n_chunks > 1) {
+  if (pl.wide_bwd)
+    grad_h_parts(p, pl.T, std::min(pl.Vc, pl.V), &pl.bwd_splits, &pl.bwd_ks);
+  if ((pl.grad_h_bf16 && pl.n_chunks > 1) || pl.bwd_splits > 1) {
     pl.off_ghp = off;
-    off = align256(off + (size_t)pl.sumd * pl.T * sizeof(float));
+    off = align256(off + (size_t)pl.bwd_splits * pl.sumd * pl.T * sizeof(float));
   }
   pl.bwd_bytes = off;
 
@@ -292,6 +357,11 @@ void make_plan(const mls_problem* p, Plan& pl) {
     off = align256(off + (size_t)rec_per_tok * pl.fb_tc);
     pl.fb_off_lab = off;
     off = align256(off + (size_t)pl.M * pl.T * sizeof(float));
+    grad_h_parts(p, pl.fb_tc, pl.V, &pl.fb_splits, &pl.fb_ks);
+    if (pl.fb_splits > 1) {
+      pl.fb_off_ghp = off;
+      off = align256(off + (size_t)pl.fb_splits * pl.sumd * pl.fb_tc * sizeof(float));
+    }
     pl.fb_bytes = off;
   } else {
     pl.fb_bytes = std::max(pl.fwd_bytes, pl.bwd_bytes);
@@ -380,6 +450,27 @@ int f32_gemm_tile(const Plan& pl, const mls_problem* p) {
   for (int i = 0; i < pl.M; ++i)
     tiles += ((pl.T + 63) / 64 + (pl.Vc + 63) / 64) * ((p->d[i] + 63) / 64);
   return tiles >= 900 ? 64 : 32;
+}
+
+// grad_h rows [t0, t0 + rows) of every sub-model from their K parts, which lie
+// one sub-model after the other ([splits][rows][d_i] each).
+hipError_t sum_parts(const mls_problem* p, int splits, int64_t rows, const float* part,
+                     void* const* grad_h, int64_t t0, hipStream_t s) {
+  SplitSumArgs a;
+  memset(&a, 0, sizeof(a));
+  a.M = p->M;
+  a.splits = splits;
+  a.accumulate = (p->flags & MLS_ACCUMULATE_GRAD_H) ? 1 : 0;
+  a.out16 = p->grad_h_dtype == MLS_BF16 ? 1 : 0;
+  const size_t es = a.out16 ? 2 : 4;
+  for (int i = 0; i < p->M; ++i) {
+    a.part[i] = part;
+    a.n[i] = rows * p->d[i];
+    a.out[i] = grad_h[i] ? static_cast<char*>(grad_h[i]) + (size_t)t0 * p->d[i] * es : nullptr;
+    part += a.n[i] * splits;
+  }
+  ProfScope ps("split_sum", s);
+  return launch_split_sum(a, s);
 }
 
 // Label logits of every token and, when `count` is set, the valid-token count
@@ -706,10 +797,13 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       // partial sums of the earlier chunks in fp32 and is stored once, by the last
       const bool last = c == pl.n_chunks - 1;
       const bool acc_flag = (p->flags & MLS_ACCUMULATE_GRAD_H) != 0;
-      float* ghp = pl.grad_h_bf16 && pl.n_chunks > 1
-                       ? reinterpret_cast<float*>(ws + pl.off_ghp) + doff[i] * pl.T
+      float* ghp = (pl.grad_h_bf16 && pl.n_chunks > 1) || pl.bwd_splits > 1
+                       ? reinterpret_cast<float*>(ws + pl.off_ghp) + doff[i] * pl.T * pl.bwd_splits
                        : nullptr;
-      if (!pl.grad_h_bf16) {
+      if (pl.bwd_splits > 1) {  // parts accumulate over the chunks, added up at the end
+        g.C = ghp;
+        g.accumulate = c > 0 ? 1 : 0;
+      } else if (!pl.grad_h_bf16) {
         g.C = static_cast<float*>(grad_h[i]);
         g.accumulate = (c > 0 || acc_flag) ? 1 : 0;
       } else if (!last) {
@@ -731,7 +825,12 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       g.tiles_n = (int)((p->d[i] + tbn - 1) / tbn);
       g.tile_begin = tiles;
       g.group_m = 8;
-      tiles += g.tiles_m * g.tiles_n;
+      if (pl.bwd_splits > 1) {
+        g.ksplit = pl.bwd_ks;
+        g.splits = (int)((g.K + g.ksplit - 1) / g.ksplit);  // fewer in a shorter last chunk
+        g.csplit = pl.T * p->d[i];
+      }
+      tiles += g.tiles_m * g.tiles_n * std::max(1, g.splits);
     }
     const int grad_h_tiles = tiles;
     for (int i = 0; i < pl.M; ++i) {
@@ -781,6 +880,10 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
                  : pl.wide_bwd ? launch_gemm_wide(ga, tiles, s) : launch_gemm_nt(ga, tiles, s);
     }
     if (e != hipSuccess) return hip_fail(e, "gradient GEMM launch");
+  }
+  if (pl.bwd_splits > 1) {
+    e = sum_parts(p, pl.bwd_splits, pl.T, reinterpret_cast<const float*>(ws + pl.off_ghp), grad_h, 0, s);
+    if (e != hipSuccess) return hip_fail(e, "grad_h sum launch");
   }
   return MLS_OK;
 }
@@ -857,6 +960,11 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
   const int64_t kt = gemm_wide_k_tile();
   const int tbm = gemm_tile_rows(true);
   const int tbn = gemm_tile_cols(true);
+  int64_t doff[kMaxModels];
+  for (int64_t i = 0, acc = 0; i < pl.M; ++i) {
+    doff[i] = acc;
+    acc += p->d[i];
+  }
   for (int c = 0; c < pl.fb_nc; ++c) {
     const int64_t t0 = (int64_t)c * pl.fb_tc;
     const int64_t tc = std::min(pl.fb_tc, pl.T - t0);
@@ -888,11 +996,17 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
       g.B = p->W[i];  // [v][d]
       g.ldb = p->d[i];
       g.cols = pl.V;
-      if (pl.grad_h_bf16)
+      if (pl.fb_splits > 1) {
+        g.C = reinterpret_cast<float*>(ws + pl.fb_off_ghp) + doff[i] * tc * pl.fb_splits;
+        g.splits = pl.fb_splits;
+        g.ksplit = pl.fb_ks;
+        g.csplit = tc * p->d[i];
+      } else if (pl.grad_h_bf16) {
         g.Cb = static_cast<uint16_t*>(grad_h[i]) + t0 * p->d[i];
-      else
+      } else {
         g.C = static_cast<float*>(grad_h[i]) + t0 * p->d[i];
-      g.accumulate = (p->flags & MLS_ACCUMULATE_GRAD_H) ? 1 : 0;
+      }
+      g.accumulate = pl.fb_splits == 1 && (p->flags & MLS_ACCUMULATE_GRAD_H) ? 1 : 0;
       g.ldc = p->d[i];
       g.ldc_rows = tc;
       g.K = round_up(pl.V, kt);
@@ -901,7 +1015,7 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
       g.tiles_n = (int)((p->d[i] + tbn - 1) / tbn);
       g.tile_begin = tiles;
       g.group_m = 8;
-      tiles += g.tiles_m * g.tiles_n;
+      tiles += g.tiles_m * g.tiles_n * std::max(1, g.splits);
     }
     const int grad_h_tiles = tiles;
     for (int i = 0; i < pl.M; ++i) {
@@ -939,6 +1053,10 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
       e = launch_gemm_wide(gm, tiles, s);
     }
     if (e != hipSuccess) return hip_fail(e, "gradient GEMM launch");
+    if (pl.fb_splits > 1) {
+      e = sum_parts(p, pl.fb_splits, tc, reinterpret_cast<const float*>(ws + pl.fb_off_ghp), grad_h, t0, s);
+      if (e != hipSuccess) return hip_fail(e, "grad_h sum launch");
+    }
   }
   e = finish_losses(p, pl, stats, ce, kl, entropy, s);
   if (e != hipSuccess) return hip_fail(e, "loss reduction launch");

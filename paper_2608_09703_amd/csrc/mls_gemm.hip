@@ -357,9 +357,10 @@ struct TileIo {
   }
 };
 
+// Tile (tm, tn) of group g, over its K part `part_k` (kind 0 groups in parts).
 template <class Mma>
-__device__ __forceinline__ void wide_tile(const GemmGroup& g, int tm, int tn, int64_t mext,
-                                          int64_t next, char* smem, int tid) {
+__device__ __forceinline__ void wide_tile(const GemmGroup& g, int tm, int tn, int part_k,
+                                          int64_t mext, int64_t next, char* smem, int tid) {
   constexpr int FM = Mma::FM;
   constexpr int FN = Mma::FN;
   const int lane = tid & 63;
@@ -373,9 +374,12 @@ __device__ __forceinline__ void wide_tile(const GemmGroup& g, int tm, int tn, in
   // stores are dropped), so each element's address is a 32-bit offset.
   const int64_t rows = mext - m0 < Mma::kBM ? mext - m0 : Mma::kBM;
   const bool out16 = g.Cb != nullptr;
+  const int64_t k0 = part_k * g.ksplit;
+  const int64_t K = g.splits > 1 && g.K - k0 > g.ksplit ? g.ksplit : g.K - k0;
+  float* const C = g.C + part_k * g.csplit;
   const __amdgpu_buffer_rsrc_t rc =
       out16 ? uniform_rsrc(reinterpret_cast<const char*>(g.Cb + m0 * g.ldc), (int)(rows * g.ldc * 2))
-            : uniform_rsrc(reinterpret_cast<const char*>(g.C + m0 * g.ldc), (int)(rows * g.ldc * 4));
+            : uniform_rsrc(reinterpret_cast<const char*>(C + m0 * g.ldc), (int)(rows * g.ldc * 4));
   const bool part = out16 && g.Cpart;
   const __amdgpu_buffer_rsrc_t rp = uniform_rsrc(
       reinterpret_cast<const char*>(part ? g.Cpart + m0 * g.ldc : g.C), part ? (int)(rows * g.ldc * 4) : 0);
@@ -398,8 +402,9 @@ __device__ __forceinline__ void wide_tile(const GemmGroup& g, int tm, int tn, in
   // so the product is added to it there and the epilogue only stores; the
   // reads' latency overlaps the first K-tile's loads.
   Mma mma;
-  mma.run_from(static_cast<const char*>(g.A), g.lda * 2, m0, g.rows, static_cast<const char*>(g.B),
-               g.ldb * 2, n0, g.cols, g.K * 2, smem, tid, [&]() {
+  mma.run_from(static_cast<const char*>(g.A) + k0 * 2, g.lda * 2, m0, g.rows,
+               static_cast<const char*>(g.B) + k0 * g.ldb * 2, g.ldb * 2, n0, g.cols - k0, K * 2,
+               smem, tid, [&]() {
                  if (!part && !acc_old)
                    mma.zero();
                  else if (inside)
@@ -422,7 +427,12 @@ __global__ __launch_bounds__(MmaH::NT, 1) void gemm_wide_kernel(GemmArgs a, int 
   for (int k = 1; k < a.ngroups; ++k)
     if (b >= a.g[k].tile_begin) gi = k;
   const GemmGroup& g = a.g[gi];
-  const int local = b - g.tile_begin;
+  int local = b - g.tile_begin;
+  int part = 0;  // K part
+  if (g.splits > 1) {
+    part = local / (g.tiles_m * g.tiles_n);
+    local -= part * g.tiles_m * g.tiles_n;
+  }
   int tm, tn;
   if (g.group_m > 0) {
     tile_coords(local, g.tiles_m, g.tiles_n, g.group_m, tm, tn);
@@ -435,9 +445,31 @@ __global__ __launch_bounds__(MmaH::NT, 1) void gemm_wide_kernel(GemmArgs a, int 
   const int64_t mext = g.ldc_rows;
   const int64_t next = g.ldc;
   if (g.kind == 0)
-    wide_tile<MmaH>(g, tm, tn, mext, next, smem, threadIdx.x);
+    wide_tile<MmaH>(g, tm, tn, part, mext, next, smem, threadIdx.x);
   else
-    wide_tile<MmaW>(g, tm, tn, mext, next, smem, threadIdx.x);
+    wide_tile<MmaW>(g, tm, tn, 0, mext, next, smem, threadIdx.x);
+}
+
+// Adds the K parts of grad_h (fixed order, so results are reproducible).
+__global__ __launch_bounds__(kThreads) void split_sum_kernel(SplitSumArgs a) {
+  const int i = blockIdx.y;
+  if (!a.out[i]) return;
+  const int64_t n = a.n[i];
+  const float* part = a.part[i];
+  for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n;
+       k += (int64_t)gridDim.x * kThreads) {
+    float v = part[k];
+#pragma unroll 4
+    for (int s = 1; s < a.splits; ++s) v += part[s * n + k];
+    if (a.out16) {
+      uint16_t* o = static_cast<uint16_t*>(a.out[i]) + k;
+      if (a.accumulate) v += __uint_as_float((uint32_t)*o << 16);
+      *o = to_storage<Bf16>(v);
+    } else {
+      float* o = static_cast<float*>(a.out[i]) + k;
+      *o = a.accumulate ? *o + v : v;
+    }
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void transpose_kernel(TransposeArgs a) {
@@ -476,6 +508,15 @@ hipError_t launch_gemm_wide(const GemmArgs& a, int total_tiles, hipStream_t stre
   if (total_tiles <= 0) return hipSuccess;
   hipLaunchKernelGGL((gemm_wide_kernel<WideGemmH, WideGemmW>), dim3(total_tiles),
                      dim3(WideGemmH::NT), 0, stream, a, total_tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_sum(const SplitSumArgs& a, hipStream_t stream) {
+  int64_t n = 0;
+  for (int i = 0; i < a.M; ++i) n = a.n[i] > n ? a.n[i] : n;
+  const int64_t blocks = (n + kThreads - 1) / kThreads;
+  const dim3 grid((unsigned)(blocks < 2048 ? blocks : 2048), (unsigned)a.M);
+  hipLaunchKernelGGL(split_sum_kernel, grid, dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -99,6 +99,11 @@ struct GemmGroup {
   // of A/B for these layouts (see WideMma::run).
   int32_t kind;
   int64_t ldc_rows;  // grad_W (kind 1): rows of C to write (the chunk's vocabulary rows)
+  // wide path, kind 0: K in `splits` parts of ksplit elements (the last may be
+  // shorter); part s goes to the fp32 matrix C + s * csplit
+  int32_t splits;
+  int64_t ksplit;
+  int64_t csplit;
 };
 
 constexpr int kMaxGemmGroups = 2 * kMaxModels;
@@ -109,6 +114,18 @@ struct GemmArgs {
   // each phase is spread evenly over the XCDs. 0 = one phase.
   int32_t phase_tiles;
   GemmGroup g[kMaxGemmGroups];
+};
+
+// out[i] = sum_s part[s * n + i] (+ out[i] with accumulate) for the grad_h of
+// every sub-model; fp32 or bf16 output, rounded once.
+struct SplitSumArgs {
+  int32_t M;
+  int32_t splits;
+  int32_t accumulate;
+  int32_t out16;
+  const float* part[kMaxModels];
+  void* out[kMaxModels];  // null: skipped
+  int64_t n[kMaxModels];
 };
 
 // dst[c][r] = src[(r0 + r) * ld_src + c] for r0 + r < src_rows, else 0;
@@ -315,6 +332,7 @@ int gemm_tile_cols(bool wide);
 hipError_t launch_gemm_wide(const GemmArgs& a, int total_tiles, hipStream_t stream);
 // fp32 path, stored layouts; tile 64 or 32 (rows and columns of a block's output)
 hipError_t launch_gemm_f32(const GemmArgs& a, int tile, int total_tiles, hipStream_t stream);
+hipError_t launch_split_sum(const SplitSumArgs& a, hipStream_t stream);
 hipError_t launch_gemm_nt(const GemmArgs& a, int total_tiles, hipStream_t stream);
 hipError_t launch_transpose(const TransposeArgs& a, int64_t max_out_rows, int64_t max_cols,
                             hipStream_t stream);

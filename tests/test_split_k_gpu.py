@@ -1,0 +1,63 @@
+"""GPU parity of grad_h products taken in K parts (few tokens against the vocabulary):
+both plans, a shorter last vocabulary chunk with fewer parts, fp32 and bf16 outputs,
+accumulation, a skipped output, and the same bits on every run."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_09703_amd import api as D
+from paper_2608_09703_amd import binding as B
+from paper_2608_09703_amd import workloads as WL
+from tests.gpu_helpers import run_fused, run_gpu, to_np
+from tests.test_parity_gpu import check_head_grads
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+CASES = [
+    # name, workload, vocab_chunk
+    ("one_chunk", WL.custom(2, 140, (64, 192), 9000, w_std=0.08, ignore_frac=0.1, seed=61), 9216),
+    ("short_last_chunk", WL.custom(3, 257, (64, 128, 320), 9000, tau=1.5, w_std=0.08, seed=62), 4096),
+    ("ragged_width", WL.custom(1, 200, (72,), 20011, w_std=0.1, seed=63), 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_k_parts(case):
+    name, wl, chunk = case
+    print(f"[k parts] {name} M={wl.M} T={wl.T} V={wl.V} dims={wl.dims}", flush=True)
+    h, W, y = WL.make_inputs(wl, device=DEV)
+    hn, Wn, yn = to_np(h), to_np(W), y.cpu().numpy()
+    g_ce, g_kl = oracle.coeffs(wl.M, -1, alpha=0.4, tau=wl.tau)
+    gh, gW = oracle.backward(hn, Wn, yn, g_ce, g_kl, tau=wl.tau)
+    sep = run_gpu(h, W, y, tau=wl.tau, g_ce=g_ce, g_kl=g_kl, vocab_chunk=chunk)
+    check_head_grads(sep, gh, gW, yn, wl.V, name)
+    fus = run_fused(h, W, y, tau=wl.tau, g_ce=g_ce, g_kl=g_kl, vocab_chunk=chunk)
+    check_head_grads(fus, gh, gW, yn, wl.V, name + " fused")
+    again = run_gpu(h, W, y, tau=wl.tau, g_ce=g_ce, g_kl=g_kl, vocab_chunk=chunk)
+    fus16 = run_fused(h, W, y, tau=wl.tau, g_ce=g_ce, g_kl=g_kl, vocab_chunk=chunk,
+                      grad_h_dtype=torch.bfloat16)
+    for i in range(wl.M):
+        assert np.array_equal(sep["grad_h"][i], again["grad_h"][i])
+        # a bf16 grad_h is the fp32 one rounded once
+        assert np.array_equal(torch.from_numpy(fus["grad_h"][i]).bfloat16().float().numpy(), fus16["grad_h"][i])
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_k_parts_accumulate_and_skip(dt):
+    """MLS_ACCUMULATE_GRAD_H adds the sum of the parts to the output once; a NULL output is skipped."""
+    wl = WL.custom(2, 150, (64, 128), 9000, w_std=0.1, seed=64)
+    h, W, y = WL.make_inputs(wl, device=DEV)
+    base = run_gpu(h, W, y, g_ce=[1.0, 1.0], g_kl=[0.5, 0.0])
+    dev = torch.device(DEV)
+    p = D.make_problem(h, W, y, flags=B.MLS_ACCUMULATE_GRAD_H, grad_h_dtype=dt)
+    buf = D.Buffers(p, dev)
+    D.forward(p, buf, dev)
+    out = torch.full(h[1].shape, 0.5, device=DEV, dtype=dt)
+    c = [torch.tensor(v, device=DEV) for v in ([1.0, 1.0], [0.5, 0.0])]
+    D.backward(p, buf, dev, c[0], c[1], [None, out], [None, None])
+    want = (torch.tensor(base["grad_h"][1], device=DEV) + 0.5).to(dt)
+    assert torch.equal(out, want)
