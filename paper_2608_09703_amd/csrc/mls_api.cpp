@@ -169,8 +169,8 @@ int64_t launch_span(int64_t n1, int64_t c1, int64_t n2, int64_t c2) {
 // 32,000: 1,502 -> 530 us. With 4,096 tokens of the headline shape one part
 // remains the shortest.
 void grad_h_parts(const mls_problem* p, int64_t rows, int64_t vrows, int* splits, int64_t* ksplit) {
-  constexpr int64_t kTileCost = 3;       // K-tiles
-  constexpr int64_t kTileBytes = 8 << 20;  // bytes at 5 TB/s in a K-tile's 1.7 us
+  constexpr int64_t kTileCost = 6;       // K-tiles
+  constexpr int64_t kTileBytes = 4 << 20;  // bytes at 5 TB/s in a K-tile's 0.8 us
   const int64_t bm = gemm_tile_rows(true), bn = gemm_tile_cols(true), bk = gemm_wide_k_tile();
   const int64_t nk = (vrows + bk - 1) / bk, nkw = (rows + bk - 1) / bk;
   int64_t cols = 0, sumd = 0;
@@ -183,7 +183,7 @@ void grad_h_parts(const mls_problem* p, int64_t rows, int64_t vrows, int* splits
   *ksplit = nk * bk;
   int64_t best = launch_span(n1, nk + kTileCost, n2, nkw + kTileCost);
   best -= best / 25;
-  for (int64_t want = 2; want <= kMaxSplits && nk / want >= 8; ++want) {
+  for (int64_t want = 2; want <= kMaxSplits && nk / want >= 16; ++want) {
     const int64_t per = (nk + want - 1) / want;
     const int64_t s = (nk + per - 1) / per;
     const int64_t t = launch_span(n1 * s, per + kTileCost, n2, nkw + kTileCost) +

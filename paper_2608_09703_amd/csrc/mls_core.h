@@ -31,13 +31,15 @@ typedef __attribute__((address_space(1))) void glb_void_t;
 // the compiler derived with vector instructions (tile coordinates from integer
 // division) would otherwise leave it in vector registers, and every buffer
 // load through it would then be wrapped in a loop over distinct descriptors.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const char* base, int bytes) {
+__device__ __forceinline__ char* uniform_ptr(const char* base) {
   const uint64_t v = reinterpret_cast<uint64_t>(base);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  void* p = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, __builtin_amdgcn_readfirstlane(bytes),
-                                           0x00020000);
+  return reinterpret_cast<char*>(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const char* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(base), (short)0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
 template <int N>
@@ -137,13 +139,8 @@ __device__ __forceinline__ uint2 lds_read_tr8(const char* p) {
   return __builtin_bit_cast(uint2, v);
 }
 
-// SPREAD: the next K-tile's loads are issued a few at a time over the first two
-// K-steps of the current one instead of in one burst after the barrier, so their
-// LDS writes interleave with the fragment reads while the last of them still
-// has half a K-tile of lead. It pays where a K-tile lasts long (the 256 x 256
-// GEMM tile), and costs where it does not (the 128 x 128 fused tiles).
 template <int BM, int BN, int WGM, int WGN, int STAGES, int RB = 128, int ALAY = kLayoutKC,
-          int BLAY = kLayoutKC, bool SPREAD = false, bool KTAIL = false>
+          int BLAY = kLayoutKC, bool KTAIL = false>
 struct WideMma {
   static constexpr int kBM = BM;
   static constexpr int kBN = BN;
@@ -165,10 +162,10 @@ struct WideMma {
   static constexpr int kLoadsPerTile = LA + LB;
   static_assert(RB == 128 || RB == 64, "LDS rows of 64 or 128 bytes");
   static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile must split evenly over the waves");
-  static_assert(STAGES >= 2 && STAGES <= 4, "2..4 stages");
+  static_assert(STAGES >= 2 && STAGES <= 5, "2..5 stages");
   static_assert(kLoadsPerTile * (STAGES - 1) < 64, "vmcnt range");
-  static_assert(!KTAIL || (RB == 128 && !SPREAD && ALAY == kLayoutKC && BLAY == kLayoutKC),
-                "K tails: K-contiguous operands, loads in one burst");
+  static_assert(!KTAIL || (RB == 128 && ALAY == kLayoutKC && BLAY == kLayoutKC),
+                "K tails: K-contiguous operands");
 
   f32x16_t acc[FM][FN];
 
@@ -210,39 +207,31 @@ struct WideMma {
     }
   }
 
-  // MC operand panel: columns from m0 on, over the `nrows` stored rows (the
-  // K extent that exists in memory); reads past the end return 0, so K-tiles
-  // beyond nrows contribute nothing.
-  __device__ __forceinline__ static __amdgpu_buffer_rsrc_t panel_rsrc_mc(const char* base,
-                                                                         int64_t ld_bytes,
-                                                                         int64_t m0, int64_t nrows) {
-    const int64_t bytes = nrows * ld_bytes - m0 * 2;
-    return uniform_rsrc(base + m0 * 2, (int)(bytes > 0 ? bytes : 0));
+  // bytes of the rows [row0, row0 + rows) that exist
+  __device__ __forceinline__ static int64_t panel_bytes(int64_t ld_bytes, int64_t row0,
+                                                        int64_t nrows, int rows) {
+    int64_t avail = nrows - row0;
+    avail = avail < rows ? avail : rows;
+    return (avail > 0 ? avail : 0) * ld_bytes;
   }
-
   __device__ __forceinline__ static __amdgpu_buffer_rsrc_t panel_rsrc(const char* base,
                                                                       int64_t ld_bytes,
                                                                       int64_t row0, int64_t nrows,
                                                                       int rows) {
-    int64_t avail = nrows - row0;
-    avail = avail < rows ? avail : rows;
-    avail = avail > 0 ? avail : 0;
-    return uniform_rsrc(base + row0 * ld_bytes, (int)(avail * ld_bytes));
+    return uniform_rsrc(base + row0 * ld_bytes, (int)panel_bytes(ld_bytes, row0, nrows, rows));
   }
 
-  // Enqueue the direct loads of one operand tile. `vofs` is added to every
-  // lane's offset (it takes part in the descriptor's range check); `sofs` is
-  // the scalar offset (not range-checked, so only used where every lane's
-  // address stays inside its row: the K position of a KC operand).
+  // Enqueue the direct loads of one KC operand tile at byte `sofs` of its rows
+  // (a scalar offset, which is not range-checked: every lane's address stays
+  // inside its row).
   template <int L>
   __device__ __forceinline__ static void issue_operand(__amdgpu_buffer_rsrc_t rsrc,
-                                                       const uint32_t* off, uint32_t vofs,
-                                                       int sofs, char* lds, int wave) {
+                                                       const uint32_t* off, int sofs, char* lds,
+                                                       int wave) {
 #pragma unroll
     for (int j = 0; j < L; ++j) {
       char* dst = lds + (j * NW + wave) * 64 * 16;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)dst, 16, off[j] + vofs, sofs, 0,
-                                               0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)dst, 16, off[j], sofs, 0, 0);
     }
   }
 
@@ -265,8 +254,9 @@ struct WideMma {
     }
   }
 
-  // Issues load j (0 .. LA + LB - 1) of one K-tile into stage `st`; ka / kb
-  // are the tile's K positions as issue_operand takes them.
+  // Issues load j (0 .. LA + LB - 1) of one K-tile into stage `st`; ka / kb are
+  // the tile's K positions: a KC operand's scalar offset (see issue_operand), an
+  // MC operand's row offset, added to the lane's (so it is range-checked).
   __device__ __forceinline__ static void issue_one(int j, __amdgpu_buffer_rsrc_t ra,
                                                    __amdgpu_buffer_rsrc_t rb, const uint32_t* offa,
                                                    const uint32_t* offb, uint32_t ka, uint32_t kb,
@@ -304,37 +294,23 @@ struct WideMma {
                                              int wm, int wn, uint4* a, uint4* b) {
     const int c = 2 * kk + (lane >> 5);
 #pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-      if (ALAY == kLayoutKC)
-        a[fm] = lds_read16_rb<RB>(sA + wm * WTM * RB, fm * 32 + (lane & 31), c);
-      else
-        a[fm] = mc_frag<BM>(sA, wm * WTM + fm * 32, kk, lane);
-    }
+    for (int fm = 0; fm < FM; ++fm)
+      a[fm] = lds_read16_rb<RB>(sA + wm * WTM * RB, fm * 32 + (lane & 31), c);
 #pragma unroll
-    for (int fn = 0; fn < FN; ++fn) {
-      if (BLAY == kLayoutKC)
-        b[fn] = lds_read16_rb<RB>(sB + wn * WTN * RB, fn * 32 + (lane & 31), c);
-      else
-        b[fn] = mc_frag<BN>(sB, wn * WTN + fn * 32, kk, lane);
-    }
+    for (int fn = 0; fn < FN; ++fn)
+      b[fn] = lds_read16_rb<RB>(sB + wn * WTN * RB, fn * 32 + (lane & 31), c);
   }
 
-  // `hook(kk)` runs at the start of K-step kk (the spread loads of the next K-tile).
-  template <class Hook>
   __device__ __forceinline__ void compute_stage(const char* sA, const char* sB, int lane, int wm,
-                                                int wn, Hook&& hook) {
+                                                int wn) {
     constexpr int kMfma = FM * FN;
-    constexpr int kReads = (FM + FN) * ((ALAY == kLayoutMC || BLAY == kLayoutMC) ? 2 : 1);
+    constexpr int kReads = FM + FN;
     constexpr int kPer = kMfma / kReads > 0 ? kMfma / kReads : 1;  // MFMAs per read
     uint4 a[2][FM], b[2][FN];
     load_frags(sA, sB, 0, lane, wm, wn, a[0], b[0]);
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) {
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (SPREAD) {
-        hook(kk);
-        __builtin_amdgcn_sched_barrier(0);
-      }
       if (kk < KSTEPS - 1) load_frags(sA, sB, kk + 1, lane, wm, wn, a[(kk + 1) & 1], b[(kk + 1) & 1]);
 #pragma unroll
       for (int fm = 0; fm < FM; ++fm)
@@ -351,10 +327,9 @@ struct WideMma {
     }
   }
 
-  // acc = A[a_row0 : +BM, :K] * B[b_row0 : +BN, :K]^T with K = kbytes / 2.
-  // a_rows / b_rows: rows of the stored operand matrix (M extent for a KC
-  // operand, K extent for an MC operand; rows beyond it read as zero).
-  // For an MC operand, a_row0 / b_row0 is the first column.
+  // acc = A[a_row0 : +BM, :K] * B[b_row0 : +BN, :K]^T with K = kbytes / 2, both
+  // operands K-contiguous; a_rows / b_rows: rows of the stored operand matrix
+  // (rows beyond it read as zero).
   // On return every wave has passed a barrier after its last LDS read, so the
   // LDS stages may be reused.
   __device__ __forceinline__ void run(const char* __restrict__ A, int64_t lda_bytes,
@@ -362,63 +337,31 @@ struct WideMma {
                                       const char* __restrict__ B, int64_t ldb_bytes,
                                       int64_t b_row0, int64_t b_rows, int64_t kbytes,
                                       char* smem, int tid) {
-    run_from(A, lda_bytes, a_row0, a_rows, B, ldb_bytes, b_row0, b_rows, kbytes, smem, tid,
-             [this]() { zero(); });
-  }
-
-  // As run(), with the accumulators set by init() instead of zeroed. init()
-  // runs before any K-tile load is issued, so loads it issues are older than
-  // the first K-tile's and are complete once that K-tile is (loads return in
-  // order): their latency hides behind the pipeline's prologue.
-  template <class Init>
-  __device__ __forceinline__ void run_from(const char* __restrict__ A, int64_t lda_bytes,
-                                           int64_t a_row0, int64_t a_rows,
-                                           const char* __restrict__ B, int64_t ldb_bytes,
-                                           int64_t b_row0, int64_t b_rows, int64_t kbytes,
-                                           char* smem, int tid, Init&& init) {
+    static_assert(ALAY == kLayoutKC && BLAY == kLayoutKC, "K-contiguous operands");
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wm = wave % WGM;
     const int wn = wave / WGM;
-    init();
+    zero();
     const int nk = KTAIL ? (int)((kbytes + RB - 1) / RB) : (int)(kbytes / RB);
-    // KC operands: panel of BM (BN) rows, K position as scalar byte offset.
-    // MC operands: panel of BM (BN) columns, K position as scalar row offset.
-    const __amdgpu_buffer_rsrc_t ra = ALAY == kLayoutKC
-                                          ? panel_rsrc(A, lda_bytes, a_row0, a_rows, BM)
-                                          : panel_rsrc_mc(A, lda_bytes, a_row0, a_rows);
-    const __amdgpu_buffer_rsrc_t rb = BLAY == kLayoutKC
-                                          ? panel_rsrc(B, ldb_bytes, b_row0, b_rows, BN)
-                                          : panel_rsrc_mc(B, ldb_bytes, b_row0, b_rows);
+    const __amdgpu_buffer_rsrc_t ra = panel_rsrc(A, lda_bytes, a_row0, a_rows, BM);
+    const __amdgpu_buffer_rsrc_t rb = panel_rsrc(B, ldb_bytes, b_row0, b_rows, BN);
     uint32_t offa[LA], offb[LB];
-    if (ALAY == kLayoutKC)
-      panel_offsets<LA>(lda_bytes, wave, lane, offa);
-    else
-      panel_offsets_mc<BM, LA>(lda_bytes, wave, lane, offa);
-    if (BLAY == kLayoutKC)
-      panel_offsets<LB>(ldb_bytes, wave, lane, offb);
-    else
-      panel_offsets_mc<BN, LB>(ldb_bytes, wave, lane, offb);
-    // K position of tile t: KC operands move along the row (scalar offset);
-    // MC operands move down BK rows (per-lane offset, range-checked).
-    const uint32_t stepa = ALAY == kLayoutKC ? (uint32_t)RB : (uint32_t)(BK * lda_bytes);
-    const uint32_t stepb = BLAY == kLayoutKC ? (uint32_t)RB : (uint32_t)(BK * ldb_bytes);
-#pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) {
-      if (s < nk) {
-        char* st = smem + s * kStageBytes;
-        const uint32_t ka = s * stepa, kb = s * stepb;
-        if (KTAIL && (s + 1) * RB > kbytes) {
-          issue_operand_tail<LA>(ra, offa, (int)ka, (int)kbytes, st, wave, lane);
-          issue_operand_tail<LB>(rb, offb, (int)kb, (int)kbytes, st + BM * RB, wave, lane);
-          continue;
-        }
-        issue_operand<LA>(ra, offa, ALAY == kLayoutKC ? 0u : ka, ALAY == kLayoutKC ? (int)ka : 0, st,
-                          wave);
-        issue_operand<LB>(rb, offb, BLAY == kLayoutKC ? 0u : kb, BLAY == kLayoutKC ? (int)kb : 0,
-                          st + BM * RB, wave);
+    panel_offsets<LA>(lda_bytes, wave, lane, offa);
+    panel_offsets<LB>(ldb_bytes, wave, lane, offb);
+    auto issue = [&](int kt) {
+      char* st = smem + (kt % STAGES) * kStageBytes;
+      if (KTAIL && (kt + 1) * RB > kbytes) {
+        issue_operand_tail<LA>(ra, offa, kt * RB, (int)kbytes, st, wave, lane);
+        issue_operand_tail<LB>(rb, offb, kt * RB, (int)kbytes, st + BM * RB, wave, lane);
+      } else {
+        issue_operand<LA>(ra, offa, kt * RB, st, wave);
+        issue_operand<LB>(rb, offb, kt * RB, st + BM * RB, wave);
       }
-    }
+    };
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s)
+      if (s < nk) issue(s);
     for (int kt = 0; kt < nk; ++kt) {
       // tiles issued after kt that may stay in flight
       const int ahead = (nk - 1 - kt) < (STAGES - 2) ? (nk - 1 - kt) : (STAGES - 2);
@@ -432,45 +375,136 @@ struct WideMma {
       // stage (kt - 1) % STAGES is refilled below: every wave's reads of it must
       // have completed
       stage_barrier();
-      const int nt = kt + STAGES - 1;
+      if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1);
       const char* stage = smem + (kt % STAGES) * kStageBytes;
-      if constexpr (!SPREAD) {
-        if (nt < nk) {
-          char* st = smem + (nt % STAGES) * kStageBytes;
-          const uint32_t ka = nt * stepa, kb = nt * stepb;
-          if (KTAIL && (nt + 1) * RB > kbytes) {
-            issue_operand_tail<LA>(ra, offa, (int)ka, (int)kbytes, st, wave, lane);
-            issue_operand_tail<LB>(rb, offb, (int)kb, (int)kbytes, st + BM * RB, wave, lane);
-          } else {
-            issue_operand<LA>(ra, offa, ALAY == kLayoutKC ? 0u : ka, ALAY == kLayoutKC ? (int)ka : 0,
-                              st, wave);
-            issue_operand<LB>(rb, offb, BLAY == kLayoutKC ? 0u : kb, BLAY == kLayoutKC ? (int)kb : 0,
-                              st + BM * RB, wave);
-          }
-        }
-        compute_stage(stage, stage + BM * RB, lane, wm, wn, [](int) {});
-      } else {
-        char* st = smem + (nt % STAGES) * kStageBytes;
-        const uint32_t ka = nt * stepa, kb = nt * stepb;
-        const bool more = nt < nk;
-        compute_stage(stage, stage + BM * RB, lane, wm, wn, [&](int kk) {
-          if (!more) return;
-          // the tile's loads in the first two K-steps, the B panel's first (on the
-          // 256 x 256 GEMM tile: B's four, then A's four; B, the head or the
-          // hidden states, is re-read from L2 less often than the slab, so its
-          // loads take longer): spread enough that their LDS writes do not land
-          // in one burst, early enough that the last ones still have half a
-          // K-tile to arrive before the next barrier
-          constexpr int kSpreadSteps = KSTEPS < 2 ? KSTEPS : 2;
-          constexpr int kPerStep = (kLoadsPerTile + kSpreadSteps - 1) / kSpreadSteps;
-#pragma unroll
-          for (int q = 0; q < kPerStep; ++q) {
-            const int j = kk * kPerStep + q;
-            if (j < kLoadsPerTile) issue_one((j + LA) % kLoadsPerTile, ra, rb, offa, offb, ka, kb, st, wave);
-          }
-        });
-      }
+      compute_stage(stage, stage + BM * RB, lane, wm, wn);
     }
+    stage_barrier();
+  }
+
+  // Fragment f (0 .. FM - 1: A, then B) of K-step kk.
+  __device__ __forceinline__ static uint4 frag(const char* st, int f, int kk, int lane, int wm,
+                                               int wn) {
+    const char* sB = st + BM * RB;
+    const int c = 2 * kk + (lane >> 5);
+    if (f < FM) {
+      if (ALAY == kLayoutKC) return lds_read16_rb<RB>(st + wm * WTM * RB, f * 32 + (lane & 31), c);
+      return mc_frag<BM>(st, wm * WTM + f * 32, kk, lane);
+    }
+    if (BLAY == kLayoutKC) return lds_read16_rb<RB>(sB + wn * WTN * RB, (f - FM) * 32 + (lane & 31), c);
+    return mc_frag<BN>(sB, wn * WTN + (f - FM) * 32, kk, lane);
+  }
+
+  // One K-step of run_pipelined(): its MFMAs on the fragments (a, b), with one
+  // fragment of the next K-step read (rd(f)) behind each of the first FM + FN and
+  // one K-tile load (ld(j)) behind each of the last ones, in exactly this order:
+  // left to itself the scheduler puts the reads and loads in one run, in which
+  // the matrix core idles.
+  template <class Rd, class Ld>
+  __device__ __forceinline__ void k_step(const uint4* a, const uint4* b, Rd&& rd, Ld&& ld) {
+    constexpr int kMfma = FM * FN;
+    constexpr int kFrags = FM + FN;
+    static_assert(kMfma >= kFrags && kMfma >= kLoadsPerTile, "a slot for every read and load");
+#pragma unroll
+    for (int m = 0; m < kMfma; ++m) {
+      mma_step<Bf16>(acc[m / FN][m % FN], a[m / FN], b[m % FN]);
+      if (m < kFrags) rd(m < FN ? FM + m : m - FN);  // B's first: the next K-step's first MFMAs need all of them
+      if (m >= kMfma - kLoadsPerTile) ld(m - (kMfma - kLoadsPerTile));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // The product for any operand layout, with the accumulators set by init() (it
+  // runs before any K-tile load is issued, so loads it issues are older than the
+  // first K-tile's and complete with it). For an MC operand a_rows / b_rows is
+  // the K extent that exists and a_row0 / b_row0 the first column.
+  //
+  // A K-tile holds two K-steps, and nothing is waited for that was not issued a
+  // K-step or more before. The barrier that publishes K-tile kt + 1 stands
+  // between the K-steps of tile kt: past it, the second one runs on fragments
+  // already in registers while the first fragments of tile kt + 1 are read, and
+  // the loads of tile kt + STAGES go to the stage of tile kt, whose reads every
+  // wave has drained, so the matrix core has work on both sides of the barrier
+  // and STAGES - 1 K-tiles stay in flight. Against two stages of 64-wide K, whose
+  // first fragments are read after the barrier, the 256 x 256 gradient GEMM with
+  // five stages of 32-wide K takes 4.22 instead of 4.36 ms per headline step
+  // (1.20 PFLOP/s), and 4 stages the same. What is left: without its loads the
+  // loop takes 3.5 ms, without its fragment reads no less, and with every tile
+  // on the same panels (all loads hit L2) 4.02, at a clock near 1.8 GHz.
+  template <class Init>
+  __device__ __forceinline__ void run_pipelined(const char* __restrict__ A, int64_t lda_bytes,
+                                                int64_t a_row0, int64_t a_rows,
+                                                const char* __restrict__ B, int64_t ldb_bytes,
+                                                int64_t b_row0, int64_t b_rows, int64_t kbytes,
+                                                char* smem, int tid, Init&& init) {
+    static_assert(KSTEPS == 2 && !KTAIL && STAGES == 5, "K-tiles of two K-steps, five stages");
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WGM;
+    const int wn = wave / WGM;
+    init();
+    const int nk = (int)(kbytes / RB);
+    // KC operands: panel of BM (BN) rows. MC operands: panel of BM (BN) columns
+    // over the stored rows; reads past them return 0. Tiles past the last are loaded like the others,
+    // through descriptors of length 0 (they read as zero, touch no memory and
+    // keep the number of loads in flight, and with it the wait below, the same).
+    const int64_t sza = ALAY == kLayoutKC ? panel_bytes(lda_bytes, a_row0, a_rows, BM)
+                                          : a_rows * lda_bytes - a_row0 * 2;
+    const int64_t szb = BLAY == kLayoutKC ? panel_bytes(ldb_bytes, b_row0, b_rows, BN)
+                                          : b_rows * ldb_bytes - b_row0 * 2;
+    const int bytes_a = __builtin_amdgcn_readfirstlane((int)(sza > 0 ? sza : 0));
+    const int bytes_b = __builtin_amdgcn_readfirstlane((int)(szb > 0 ? szb : 0));
+    char* const pa = uniform_ptr(A + (ALAY == kLayoutKC ? a_row0 * lda_bytes : a_row0 * 2));
+    char* const pb = uniform_ptr(B + (BLAY == kLayoutKC ? b_row0 * ldb_bytes : b_row0 * 2));
+    uint32_t offa[LA], offb[LB];
+    if (ALAY == kLayoutKC)
+      panel_offsets<LA>(lda_bytes, wave, lane, offa);
+    else
+      panel_offsets_mc<BM, LA>(lda_bytes, wave, lane, offa);
+    if (BLAY == kLayoutKC)
+      panel_offsets<LB>(ldb_bytes, wave, lane, offb);
+    else
+      panel_offsets_mc<BN, LB>(ldb_bytes, wave, lane, offb);
+    const uint32_t stepa = ALAY == kLayoutKC ? (uint32_t)RB : (uint32_t)(BK * lda_bytes);
+    const uint32_t stepb = BLAY == kLayoutKC ? (uint32_t)RB : (uint32_t)(BK * ldb_bytes);
+    auto rd = [&](int f, int slot, int kk, uint4* a, uint4* b) {
+      const uint4 v = frag(smem + slot * kStageBytes, f, kk, lane, wm, wn);
+      if (f < FM)
+        a[f] = v;
+      else
+        b[f - FM] = v;
+    };
+    auto ld = [&](int j, int kt, int slot) {
+      const bool in = kt < nk;
+      issue_one((j + LA) % kLoadsPerTile,
+                __builtin_amdgcn_make_buffer_rsrc(pa, (short)0, in ? bytes_a : 0, 0x00020000),
+                __builtin_amdgcn_make_buffer_rsrc(pb, (short)0, in ? bytes_b : 0, 0x00020000), offa,
+                offb, kt * stepa, kt * stepb, smem + slot * kStageBytes, wave);
+    };
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s)
+#pragma unroll
+      for (int j = 0; j < kLoadsPerTile; ++j) ld(j, s, s);
+    wait_vmcnt<(STAGES - 1) * kLoadsPerTile>();
+    stage_barrier();
+    uint4 a0[FM], b0[FN], a1[FM], b1[FN];
+#pragma unroll
+    for (int f = 0; f < FM + FN; ++f) rd(f, 0, 0, a0, b0);
+    int slot = 0;
+#pragma unroll 1
+    for (int kt = 0; kt < nk; ++kt) {
+      const int next = slot == STAGES - 1 ? 0 : slot + 1;
+      __builtin_amdgcn_sched_barrier(0);
+      k_step(a0, b0, [&](int f) { rd(f, slot, 1, a1, b1); }, [](int) {});
+      wait_vmcnt<(STAGES - 2) * kLoadsPerTile>();
+      stage_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      // (past the last tile: fragments of a stage of zeros, which nothing uses)
+      k_step(a1, b1, [&](int f) { rd(f, next, 0, a0, b0); },
+             [&](int j) { ld(j, kt + STAGES, slot); });
+      slot = next;
+    }
+    wait_vmcnt<0>();
     stage_barrier();
   }
 

@@ -1096,8 +1096,8 @@ using HeadWide = WideMma<128, 128, 2, 2, 2>;
 // 192 vocabulary rows: 80 KB of stages, two blocks fill a CU's LDS
 using HeadWide192 = WideMma<192, 128, 2, 2, 2>;
 // widths that are not multiples of the 64-wide K-tile
-using HeadWideTail = WideMma<128, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
-using HeadWide192Tail = WideMma<192, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
+using HeadWideTail = WideMma<128, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
+using HeadWide192Tail = WideMma<192, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
 using HeadGenF32 = TileMma<F32, 128, 128, 2, 2>;
 
 }  // namespace

@@ -305,9 +305,9 @@ __global__ __launch_bounds__(kRedThreads) void diag_mean_kernel(DiagArgs a) {
 using DiagWide = WideMma<kFusedWideBM, kDiagBN, 2, 2, 2>;
 using DiagWide4 = WideMma<kFusedWideBM, kDiagBN / 2, 2, 2, 2>;
 using DiagWideTail =
-    WideMma<kFusedWideBM, kDiagBN, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
+    WideMma<kFusedWideBM, kDiagBN, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
 using DiagWide4Tail =
-    WideMma<kFusedWideBM, kDiagBN / 2, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
+    WideMma<kFusedWideBM, kDiagBN / 2, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
 template <typename E>
 using DiagGen = TileMma<E, kFusedBM, kDiagGenBN, 2, 2>;
 

@@ -39,7 +39,7 @@ using GenMmaBf16 = TileMma<Bf16, kFusedBM, kFusedBN, 2, 2>;
 using MmaF32 = TileMma<F32, kFusedF32, kFusedF32, 2, 2>;
 using WideFused = WideMma<kFusedWideBM, kFusedBN, 2, 2, 2>;  // 2 blocks per CU
 using WideFusedTail =
-    WideMma<kFusedWideBM, kFusedBN, 2, 2, 2, 128, kLayoutKC, kLayoutKC, false, true>;
+    WideMma<kFusedWideBM, kFusedBN, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
 
 // Per-lane copy of the teacher's tile values (its softmax weights), laid out
 // like the accumulators. The bf16 paths keep them as packed fp16 pairs (half

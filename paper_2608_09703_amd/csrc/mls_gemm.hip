@@ -213,15 +213,15 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmArgs a) {
     f32_tile<BM, BN, KS, true>(g, tm, tn, smem, threadIdx.x);
 }
 
-// bf16 path: 256 x 256 tiles, 8 waves (2 per SIMD), direct-to-LDS loads, 2
-// stages of 64-wide K (each K-tile reads whole 128-byte lines of a K-contiguous
-// operand); the next K-tile's loads are spread over the current one's K-steps. The head chunk (grad_h) and the slab and h (grad_W) are
-// read in their stored layouts through transposing LDS reads, so no operand is
-// ever transposed in memory.
+// bf16 path: 256 x 256 tiles, 8 waves (2 per SIMD) of 128 x 64, direct-to-LDS
+// loads, five stages of 32-wide K (all 160 KB of LDS; see run_pipelined). The
+// head chunk (grad_h) and the slab and h (grad_W) are read in their stored
+// layouts through transposing LDS reads, so no operand is ever transposed in
+// memory.
 constexpr int kWideBM = 256;
 constexpr int kWideBN = 256;
-using WideGemmH = WideMma<kWideBM, kWideBN, 2, 4, 2, 128, kLayoutKC, kLayoutMC, true>;
-using WideGemmW = WideMma<kWideBM, kWideBN, 2, 4, 2, 128, kLayoutMC, kLayoutMC, true>;
+using WideGemmH = WideMma<kWideBM, kWideBN, 2, 4, 5, 64, kLayoutKC, kLayoutMC>;
+using WideGemmW = WideMma<kWideBM, kWideBN, 2, 4, 5, 64, kLayoutMC, kLayoutMC>;
 
 // Loads and stores of one wave's part of an output tile through buffer
 // descriptors over the tile's existing rows (rows past them read as 0 and are
@@ -402,7 +402,7 @@ __device__ __forceinline__ void wide_tile(const GemmGroup& g, int tm, int tn, in
   // so the product is added to it there and the epilogue only stores; the
   // reads' latency overlaps the first K-tile's loads.
   Mma mma;
-  mma.run_from(static_cast<const char*>(g.A) + k0 * 2, g.lda * 2, m0, g.rows,
+  mma.run_pipelined(static_cast<const char*>(g.A) + k0 * 2, g.lda * 2, m0, g.rows,
                static_cast<const char*>(g.B) + k0 * g.ldb * 2, g.ldb * 2, n0, g.cols - k0, K * 2,
                smem, tid, [&]() {
                  if (!part && !acc_old)
