@@ -75,8 +75,10 @@ enum mls_mode {
 enum mls_flags {
   MLS_ACCUMULATE_GRAD_W = 1u, /* grad_W_i += instead of = */
   MLS_ACCUMULATE_GRAD_H = 2u, /* grad_h_i += instead of = */
-  MLS_FWD_BWD_RECOMPUTE = 4u  /* mls_distill_fwd_bwd: recompute the logits in the backward
+  MLS_FWD_BWD_RECOMPUTE = 4u, /* mls_distill_fwd_bwd: recompute the logits in the backward
                                  instead of storing them per token chunk */
+  MLS_GRAD_W_BF16 = 8u        /* mls_distill_bwd: the grad_W_i are bfloat16 (rounded once
+                                 from the fp32 sums); mls_distill_fwd_bwd refuses it */
 };
 
 /* Device-side error bits written into the statistics buffer by the forward. */
@@ -191,7 +193,9 @@ mls_status mls_distill_fwd(const mls_problem* p, void* stats, float* ce, float* 
  *                that gradient. Overwritten unless MLS_ACCUMULATE_GRAD_H (a bf16
  *                grad_h is then read, added to in fp32 and rounded once).
  *   grad_W       host array of M device pointers; an entry may be NULL.
- *                Overwritten unless MLS_ACCUMULATE_GRAD_W.
+ *                Overwritten unless MLS_ACCUMULATE_GRAD_W (a bf16 grad_W is then
+ *                read, added to in fp32 and rounded once). With MLS_GRAD_W_BF16
+ *                the pointers are to bfloat16 arrays of the same shapes.
  * Asynchronous on stream.
  */
 mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float* g_ce,

@@ -96,9 +96,10 @@ def backward(p: B.Problem, buf: Buffers, device, g_ce: Optional[torch.Tensor],
     for g in grad_h:
         if g is not None and (g.dtype != gh_dt or not g.is_contiguous()):
             raise ValueError(f"grad_h tensors are contiguous {gh_dt} tensors")
+    gW_dt = torch.bfloat16 if p.flags & B.MLS_GRAD_W_BF16 else torch.float32
     for g in grad_W:
-        if g is not None and (g.dtype != torch.float32 or not g.is_contiguous()):
-            raise ValueError("grad_W tensors are contiguous float32 tensors")
+        if g is not None and (g.dtype != gW_dt or not g.is_contiguous()):
+            raise ValueError(f"grad_W tensors are contiguous {gW_dt} tensors")
     gc = g_ce.data_ptr() if g_ce is not None else None
     gk = g_kl.data_ptr() if g_kl is not None else None
     B.distill_bwd(p, buf.stats.data_ptr(), gc, gk,
@@ -112,8 +113,9 @@ class _Distill(torch.autograd.Function):
     def forward(ctx, labels, opts, *hw):
         M = len(hw) // 2
         h, W = list(hw[:M]), list(hw[M:])
-        # bf16 hidden states get bf16 gradients straight from the library
-        p = make_problem(h, W, labels, grad_h_dtype=h[0].dtype, **opts)
+        # bf16 hidden states and heads get bf16 gradients straight from the library
+        p = make_problem(h, W, labels, grad_h_dtype=h[0].dtype,
+                         flags=B.MLS_GRAD_W_BF16 if h[0].dtype == torch.bfloat16 else 0, **opts)
         dev = h[0].device
         buf = Buffers(p, dev)
         forward(p, buf, dev)
@@ -139,18 +141,11 @@ class _Distill(torch.autograd.Function):
         need = ctx.needs_input_grad[2:]
         gh: List[Optional[torch.Tensor]] = []
         gW: List[Optional[torch.Tensor]] = []
-        gh_dt = torch.bfloat16 if ctx.p.grad_h_dtype == B.MLS_BF16 else torch.float32
-        for i in range(M):
-            gh.append(torch.empty(hw[i].shape, dtype=gh_dt, device=dev) if need[i] else None)
-            gW.append(torch.empty(hw[M + i].shape, dtype=torch.float32, device=dev)
-                      if need[M + i] else None)
+        for i in range(M):  # of the inputs' dtype, as forward() set the problem up
+            gh.append(torch.empty_like(hw[i]) if need[i] else None)
+            gW.append(torch.empty_like(hw[M + i]) if need[M + i] else None)
         backward(ctx.p, ctx.buf, dev, g_ce, g_kl, gh, gW)
-        out = [None, None]
-        for i in range(M):
-            out.append(gh[i].to(hw[i].dtype) if gh[i] is not None else None)
-        for i in range(M):
-            out.append(gW[i].to(hw[M + i].dtype) if gW[i] is not None else None)
-        return tuple(out)
+        return (None, None, *gh, *gW)
 
 
 def distill(h_list: Sequence[torch.Tensor], W_list: Sequence[torch.Tensor], labels: torch.Tensor,

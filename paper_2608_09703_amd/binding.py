@@ -38,6 +38,7 @@ MLS_JUNCTION_ACCUMULATE = 1
 MLS_ACCUMULATE_GRAD_W = 1
 MLS_ACCUMULATE_GRAD_H = 2
 MLS_FWD_BWD_RECOMPUTE = 4
+MLS_GRAD_W_BF16 = 8
 
 MLS_DEVFLAG_LABEL_RANGE = 1
 MLS_DEVFLAG_NONFINITE = 2

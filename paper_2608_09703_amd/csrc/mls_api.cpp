@@ -662,7 +662,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     return fail(MLS_INVALID_ARG, "misaligned stats / workspace");
   for (int i = 0; i < p->M; ++i) {
     if ((grad_h[i] && !aligned(grad_h[i], p->grad_h_dtype == MLS_BF16 ? 2 : 4)) ||
-        (grad_W[i] && !aligned(grad_W[i], 4)))
+        (grad_W[i] && !aligned(grad_W[i], (p->flags & MLS_GRAD_W_BF16) ? 2 : 4)))
       return fail(MLS_INVALID_ARG, "misaligned gradient pointer %d", i);
   }
   Plan pl;
@@ -851,7 +851,13 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
         g.ldb = pl.T_pad;
         g.cols = p->d[i];
       }
-      g.C = grad_W[i] + v0 * p->d[i];
+      // each vocabulary row is complete in its chunk's launch: a bf16 output
+      // needs no fp32 copy in between (3B-suite heads at T = 4,096 through
+      // autograd: 11.71 -> 11.19 ms)
+      if (p->flags & MLS_GRAD_W_BF16)
+        g.Cb = reinterpret_cast<uint16_t*>(grad_W[i]) + v0 * p->d[i];
+      else
+        g.C = grad_W[i] + v0 * p->d[i];
       g.ldc = p->d[i];
       g.ldc_rows = vrows;
       g.K = pl.f32 ? pl.T : pl.T_pad;
@@ -910,6 +916,8 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
     return fail(MLS_INVALID_ARG, "stats, ce, kl, workspace, grad_h and grad_W must be non-NULL");
   if ((g_ce == nullptr) != (g_kl == nullptr))
     return fail(MLS_INVALID_ARG, "g_ce and g_kl must both be given or both be NULL");
+  if (p->flags & MLS_GRAD_W_BF16)
+    return fail(MLS_UNSUPPORTED, "bf16 grad_W: mls_distill_bwd only");
   if (!aligned(stats, 16) || !aligned(workspace, 16) || !aligned(ce, 4) || !aligned(kl, 4))
     return fail(MLS_INVALID_ARG, "misaligned stats / workspace / loss pointer");
   for (int i = 0; i < p->M; ++i) {
