@@ -1332,8 +1332,9 @@ mls_status mls_head_logits(int64_t T, int64_t V, int64_t d, int32_t dtype, const
   a.W = W;
   a.logits = logits;
   const bool wide = dtype == MLS_BF16;
-  a.n_tt = (int)((T + head_tile() - 1) / head_tile());
-  const int rows = head_tile_rows(wide, a.n_tt);
+  int rows, cols;
+  head_tile(wide, T, V, &rows, &cols);
+  a.n_tt = (int)((T + cols - 1) / cols);
   a.n_vt = (int)((V + rows - 1) / rows);
   // tile order (groups of vocabulary tiles), measured on the verifier's 714
   // rows with 192-row tiles: groups of 2 or 4 0.731-0.742 ms per decode step,
@@ -1343,7 +1344,7 @@ mls_status mls_head_logits(int64_t T, int64_t V, int64_t d, int32_t dtype, const
   hipError_t e;
   {
     ProfScope ps("head_logits", st);
-    e = launch_head_logits(a, dtype == MLS_F32, rows, st);
+    e = launch_head_logits(a, dtype == MLS_F32, st);
   }
   if (e != hipSuccess) return hip_fail(e, "head logits launch");
   return MLS_OK;

@@ -41,7 +41,7 @@ namespace {
 // ---------------------------------------------------------------------------
 
 template <class Mma, typename E>
-__global__ __launch_bounds__(Mma::NT, 2) void head_logits_kernel(HeadArgs a) {
+__global__ __launch_bounds__(Mma::NT, Mma::kBM == 64 ? 1 : 2) void head_logits_kernel(HeadArgs a) {
   constexpr int BM = Mma::kBM;  // vocabulary rows
   constexpr int BN = Mma::kBN;  // tokens
   constexpr int FM = Mma::FM;
@@ -1095,19 +1095,39 @@ __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
 using HeadWide = WideMma<128, 128, 2, 2, 2>;
 // 192 vocabulary rows: 80 KB of stages, two blocks fill a CU's LDS
 using HeadWide192 = WideMma<192, 128, 2, 2, 2>;
+// few rows: a quarter (half) of the token columns, so that more K-tiles of the
+// head fit in flight: 36 (32) KB per block, three blocks per CU
+using HeadFew = WideMma<64, 32, 2, 1, 4>;
+using HeadSome = WideMma<64, 64, 2, 2, 3>;
+// 128 columns, vocabularies too small for a 128-row block per CU
+using HeadShort = WideMma<64, 128, 2, 2, 3>;
 // widths that are not multiples of the 64-wide K-tile
+using HeadShortTail = WideMma<64, 128, 2, 2, 3, 128, kLayoutKC, kLayoutKC, true>;
+using HeadFewTail = WideMma<64, 32, 2, 1, 4, 128, kLayoutKC, kLayoutKC, true>;
+using HeadSomeTail = WideMma<64, 64, 2, 2, 3, 128, kLayoutKC, kLayoutKC, true>;
 using HeadWideTail = WideMma<128, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
 using HeadWide192Tail = WideMma<192, 128, 2, 2, 2, 128, kLayoutKC, kLayoutKC, true>;
 using HeadGenF32 = TileMma<F32, 128, 128, 2, 2>;
 
 }  // namespace
 
-int head_tile() { return 128; }
-// Vocabulary rows of a head tile. With at least four token tiles (the
-// verifier's rows) the 192-row tile on the wide path: at 102 x 7 rows and
-// V = 49,152 it makes 1,536 blocks, three full rounds of two blocks per CU,
-// where 128-row tiles make 2,304 (four and a half).
-int head_tile_rows(bool wide, int n_tt) { return wide && n_tt >= 4 ? 192 : 128; }
+// Tile of the head product (vocabulary rows x token columns).
+// - At most 64 rows of hidden states: bound by the head's bytes and by how many
+//   of them are in flight, so 64 vocabulary rows and 32 or 64 columns, whose
+//   stages leave room for three K-tiles ahead in three blocks per CU. One row at
+//   width 4,352, V = 49,152: 84 -> 74 us (5.8 TB/s); 16 rows at width 2,048, V =
+//   16,000: 31 -> 16 us; 64 rows at width 4,352: 94 -> 91 us.
+// - 128 columns otherwise. Where 128-row tiles would not give every CU a block,
+//   64 rows: 102 rows at width 2,048, V = 16,000 (125 blocks) 36 -> 22 us, V =
+//   32,000 (250 blocks) 41.6 -> 39.7; at 313 blocks 27.9 -> 30.0, so not there.
+// - From four such token tiles on (the verifier's rows) 192 vocabulary rows: at
+//   102 x 7 rows and V = 49,152 that makes 1,536 blocks, three full rounds of two
+//   blocks per CU, where 128-row tiles make 2,304 (four and a half).
+void head_tile(bool wide, int64_t T, int64_t V, int* rows, int* cols) {
+  *cols = !wide || T > 64 ? 128 : T > 32 ? 64 : 32;
+  const int64_t blocks = ((T + 127) / 128) * ((V + 127) / 128);  // of 128 x 128
+  *rows = !wide ? 128 : T <= 64 || blocks < 256 ? 64 : T > 3 * 128 ? 192 : 128;
+}
 int row_elems_per_thread(int64_t V) {
   for (int e : {16, 32, 48, 64})
     if (V <= (int64_t)e * kRowThreads) return e;
@@ -1120,11 +1140,20 @@ static void launch_head_t(const HeadArgs& a, hipStream_t stream) {
                      dim3(Mma::NT), 0, stream, a);
 }
 
-hipError_t launch_head_logits(const HeadArgs& a, bool f32, int rows, hipStream_t stream) {
-  if (rows != head_tile_rows(!f32, a.n_tt)) return hipErrorInvalidValue;
+hipError_t launch_head_logits(const HeadArgs& a, bool f32, hipStream_t stream) {
+  int rows, cols;
+  head_tile(!f32, a.T, a.V, &rows, &cols);
+  if (a.n_vt != (int)((a.V + rows - 1) / rows) || a.n_tt != (int)((a.T + cols - 1) / cols))
+    return hipErrorInvalidValue;
   const bool tail = a.d % 64 != 0;
   if (f32)
     launch_head_t<HeadGenF32, F32>(a, stream);
+  else if (cols == 32)
+    tail ? launch_head_t<HeadFewTail, Bf16>(a, stream) : launch_head_t<HeadFew, Bf16>(a, stream);
+  else if (cols == 64)
+    tail ? launch_head_t<HeadSomeTail, Bf16>(a, stream) : launch_head_t<HeadSome, Bf16>(a, stream);
+  else if (rows == 64)
+    tail ? launch_head_t<HeadShortTail, Bf16>(a, stream) : launch_head_t<HeadShort, Bf16>(a, stream);
   else if (rows == 192)
     tail ? launch_head_t<HeadWide192Tail, Bf16>(a, stream) : launch_head_t<HeadWide192, Bf16>(a, stream);
   else

@@ -347,11 +347,11 @@ bool junction_shape(int64_t width, int* tpr, int* cpl);
 int64_t junction_max_width();
 hipError_t launch_junction_fwd(const JunctionArgs& a, bool act_f32, hipStream_t stream);
 hipError_t launch_junction_bwd(const JunctionArgs& a, bool act_f32, bool grad_f32, hipStream_t stream);
-int head_tile();  // token rows of a head tile
-int head_tile_rows(bool wide, int n_tt);  // wide: bf16; vocabulary rows of a head tile (128 or 192)
+// wide: bf16; vocabulary rows and token columns of a head tile over T rows of V logits
+void head_tile(bool wide, int64_t T, int64_t V, int* rows, int* cols);
 int row_elems_per_thread(int64_t V);
-// rows: head_tile_rows(!f32, a.n_tt) (checked)
-hipError_t launch_head_logits(const HeadArgs& a, bool f32, int rows, hipStream_t stream);
+// n_vt and n_tt as head_tile's tile gives them (checked)
+hipError_t launch_head_logits(const HeadArgs& a, bool f32, hipStream_t stream);
 hipError_t launch_sample(const SampleArgs& a, int ept, hipStream_t stream);
 hipError_t launch_row_params(const RowParamArgs& a, int ept, hipStream_t stream);
 hipError_t launch_verify(const VerifyArgs& a, int ept, hipStream_t stream);
