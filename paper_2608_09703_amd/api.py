@@ -15,11 +15,18 @@ on caller-visible buffers (used by the tests and the benchmark).
 
 from __future__ import annotations
 
+import functools
 from typing import List, Optional, Sequence
 
 import torch
 
 from . import binding as B
+
+# Descriptors are built once per set of values (bounded) and only ever read: a
+# decoding loop makes the same few calls over and over, and filling the ctypes
+# fields costs about as much as the launch.
+_make_junction = functools.lru_cache(maxsize=256)(B.make_junction)
+_make_sampling = functools.lru_cache(maxsize=256)(B.make_sampling)
 
 
 def _dtype_code(dt: torch.dtype) -> int:
@@ -60,6 +67,9 @@ def make_problem(h: Sequence[torch.Tensor], W: Sequence[torch.Tensor], labels: t
 
 
 def _stream(dev) -> int:
+    """Handle of the device's current stream (of a tensor's device without building a Stream object)."""
+    if isinstance(dev, torch.device) and dev.index is not None:
+        return torch._C._cuda_getCurrentRawStream(dev.index)
     return torch.cuda.current_stream(dev).cuda_stream
 
 
@@ -119,12 +129,15 @@ class _Distill(torch.autograd.Function):
         dev = h[0].device
         buf = Buffers(p, dev)
         forward(p, buf, dev)
+        # the losses are the function's outputs; the context keeps the rest
+        ce, kl, entropy = buf.ce, buf.kl, buf.entropy
+        buf.ce = buf.kl = buf.entropy = None
         ctx.p = p
         ctx.buf = buf
         ctx.M = M
         ctx.save_for_backward(labels, *hw)
-        ctx.mark_non_differentiable(buf.entropy)
-        return buf.ce.clone(), buf.kl.clone(), buf.entropy.clone()
+        ctx.mark_non_differentiable(entropy)
+        return ce, kl, entropy
 
     @staticmethod
     def backward(ctx, g_ce, g_kl, g_ent):
@@ -184,24 +197,25 @@ def diagnostics(h_list: Sequence[torch.Tensor], W_list: Sequence[torch.Tensor],
     return kl, agree, am
 
 
+_JUNCTION_LAYOUTS = {"prev_first": B.MLS_JUNCTION_PREV_FIRST, "fresh_first": B.MLS_JUNCTION_FRESH_FIRST}
+
+
 def _junction_desc(o, e, grad_dtype, layout, flags=0):
-    if o.device.type != "cuda" or e.device != o.device:
+    if not o.is_cuda or e.device != o.device:
         raise RuntimeError("the junction runs on the GPU only")
-    if o.dim() != 2 or e.dim() != 2 or o.shape[0] != e.shape[0] or o.dtype != e.dtype:
+    if o.dim() != 2 or e.dim() != 2 or o.size(0) != e.size(0) or o.dtype != e.dtype:
         raise ValueError("o [T, d_prev] and e [T, d_fresh] must share T and dtype")
     if not (o.is_contiguous() and e.is_contiguous()):
         raise ValueError("o and e must be contiguous")
-    lay = {"prev_first": B.MLS_JUNCTION_PREV_FIRST, "fresh_first": B.MLS_JUNCTION_FRESH_FIRST}[layout]
-    return B.make_junction(o.shape[0], o.shape[1], e.shape[1], _dtype_code(o.dtype),
-                           _dtype_code(grad_dtype), lay, flags)
+    return _make_junction(o.size(0), o.size(1), e.size(1), _dtype_code(o.dtype),
+                          _dtype_code(grad_dtype), _JUNCTION_LAYOUTS[layout], flags)
 
 
 def junction_forward(o: torch.Tensor, e: torch.Tensor, *, layout: str = "prev_first",
                      out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Eq. (1): ``x = [o * ||e|| / ||o|| | e]`` per token (no autograd)."""
     j = _junction_desc(o, e, o.dtype, layout)
-    x = out if out is not None else torch.empty(o.shape[0], o.shape[1] + e.shape[1],
-                                                 dtype=o.dtype, device=o.device)
+    x = out if out is not None else o.new_empty((j.T, j.d_prev + j.d_fresh))
     B.junction_fwd(j, o.data_ptr(), e.data_ptr(), x.data_ptr(), _stream(o.device))
     return x
 
@@ -214,9 +228,9 @@ def junction_backward(o: torch.Tensor, e: torch.Tensor, g_x: torch.Tensor, *,
         raise ValueError("g_x must be a contiguous [T, d_prev + d_fresh] tensor")
     j = _junction_desc(o, e, g_x.dtype, layout, B.MLS_JUNCTION_ACCUMULATE if accumulate else 0)
     if g_o is None:
-        g_o = torch.empty(o.shape, dtype=g_x.dtype, device=o.device)
+        g_o = g_x.new_empty(o.shape, device=o.device)
     if g_e is None:
-        g_e = torch.empty(e.shape, dtype=g_x.dtype, device=o.device)
+        g_e = g_x.new_empty(e.shape, device=o.device)
     for g in (g_o, g_e):
         if g.dtype != g_x.dtype or not g.is_contiguous():
             raise ValueError("g_o / g_e must be contiguous and of g_x's dtype")
@@ -246,7 +260,7 @@ def junction(o: torch.Tensor, e: torch.Tensor, *, layout: str = "prev_first") ->
 
 def head_logits(o: torch.Tensor, W: torch.Tensor, out: Optional[torch.Tensor] = None):
     """``logits [T, V] = o W^T`` in fp32 through the HIP head kernel (decode regime)."""
-    if o.device.type != "cuda" or W.device != o.device or o.dtype != W.dtype:
+    if not o.is_cuda or W.device != o.device or o.dtype != W.dtype:
         raise RuntimeError("o and W must be GPU tensors of one dtype")
     if not (o.is_contiguous() and W.is_contiguous()) or o.shape[1] != W.shape[1]:
         raise ValueError("o [T, d] and W [V, d] must be contiguous with a shared d")
@@ -255,10 +269,6 @@ def head_logits(o: torch.Tensor, W: torch.Tensor, out: Optional[torch.Tensor] = 
     B.head_logits(T, V, o.shape[1], _dtype_code(o.dtype), o.data_ptr(), W.data_ptr(),
                   out.data_ptr(), _stream(o.device))
     return out
-
-
-def _sampling(V, temperature, top_p, greedy):
-    return B.make_sampling(V, temperature, top_p, greedy)
 
 
 def sample(logits: torch.Tensor, u: Optional[torch.Tensor], *, temperature: float = 1.0,
@@ -278,7 +288,7 @@ def sample(logits: torch.Tensor, u: Optional[torch.Tensor], *, temperature: floa
                                params.numel() < rows * B.ROW_PARAMS_BYTES):
         raise ValueError("params must be a contiguous uint8 tensor of rows * ROW_PARAMS_BYTES")
     tok = torch.empty(rows, dtype=torch.int32, device=logits.device)
-    B.sample(_sampling(V, temperature, top_p, greedy), rows, logits.data_ptr(),
+    B.sample(_make_sampling(V, float(temperature), float(top_p), bool(greedy)), rows, logits.data_ptr(),
              u.data_ptr() if u is not None else None, tok.data_ptr(), _stream(logits.device),
              params.data_ptr() if params is not None else None)
     return tok
@@ -319,7 +329,7 @@ def spec_verify(draft_logits: Optional[torch.Tensor], target_logits: torch.Tenso
                                      not draft_params.is_contiguous() or
                                      draft_params.numel() < G * Bt * B.ROW_PARAMS_BYTES):
         raise ValueError("draft_params must be contiguous uint8 of gamma * B records")
-    B.spec_verify(_sampling(V, temperature, top_p, greedy), Bt, G, ptr(draft_logits),
+    B.spec_verify(_make_sampling(V, float(temperature), float(top_p), bool(greedy)), Bt, G, ptr(draft_logits),
                   target_logits.data_ptr(), ptr(draft_tokens), ptr(u_accept), ptr(u_sample),
                   n_acc.data_ptr(), nxt.data_ptr(), ptr(ws), ws_bytes, _stream(dev),
                   draft_params=ptr(draft_params))

@@ -1,0 +1,68 @@
+"""The front end's cached descriptors and raw stream handles: settings that hash by
+identity are taken by value, descriptors are not mixed up between calls, and every
+form of device that names a stream still does."""
+
+import pytest
+import torch
+
+from paper_2608_09703_amd import api as D
+from paper_2608_09703_amd import binding as B
+
+
+def test_cached_descriptors_carry_their_own_values():
+    a = D._make_sampling(1000, 0.4, 0.9, False)
+    b = D._make_sampling(1000, 0.5, 0.9, False)
+    c = D._make_sampling(1000, 0.4, 0.9, True)
+    assert (a.temperature, b.temperature, c.greedy) == (pytest.approx(0.4), 0.5, 1)
+    assert D._make_sampling(1000, 0.4, 0.9, False) is a and a.greedy == 0
+    j = D._make_junction(5, 64, 128, B.MLS_BF16, B.MLS_F32, B.MLS_JUNCTION_FRESH_FIRST, 0)
+    k = D._make_junction(5, 64, 128, B.MLS_F32, B.MLS_F32, B.MLS_JUNCTION_FRESH_FIRST, 0)
+    assert (j.T, j.d_prev, j.d_fresh, j.act_dtype, k.act_dtype) == (5, 64, 128, B.MLS_BF16, B.MLS_F32)
+    assert D._make_junction.cache_info().maxsize == D._make_sampling.cache_info().maxsize == 256
+
+
+@pytest.mark.gpu
+def test_settings_as_tensors_are_read_on_every_call():
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    logits = torch.randn(64, 500, generator=g, device="cuda:0")
+    u = torch.rand(64, generator=g, device="cuda:0")
+    t = torch.tensor(0.4)
+    first = D.sample(logits, u, temperature=t)
+    t.fill_(2.0)
+    second = D.sample(logits, u, temperature=t)
+    assert torch.equal(first, D.sample(logits, u, temperature=0.4))
+    assert torch.equal(second, D.sample(logits, u, temperature=2.0)) and not torch.equal(first, second)
+
+
+@pytest.mark.gpu
+def test_stream_handles():
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.current_stream(), side):
+        with torch.cuda.stream(stream):
+            for dev in (torch.device("cuda:0"), torch.device("cuda"), "cuda:0", 0, None):
+                assert D._stream(dev) == stream.cuda_stream
+
+
+@pytest.mark.gpu
+def test_losses_are_outputs_of_their_own():
+    """The losses of two calls do not share memory, and dropping them frees the context."""
+    import gc
+    h = [torch.randn(130, 64, device="cuda:0").bfloat16().requires_grad_(True)]
+    W = [torch.randn(300, 64, device="cuda:0").bfloat16().requires_grad_(True)]
+    y = torch.randint(0, 300, (130,), device="cuda:0")
+    a = D.distill(h, W, y)
+    b = D.distill(h, W, y)
+    assert all(p.data_ptr() != q.data_ptr() and torch.equal(p, q) for p, q in zip(a, b))
+    a[0].sum().backward()
+    del a, b
+    h[0].grad = W[0].grad = None
+    gc.collect()
+    gc.disable()  # no cycle: the graph goes with its last reference
+    try:
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_allocated()
+        for _ in range(3):
+            D.distill(h, W, y)
+        assert torch.cuda.memory_allocated() == before
+    finally:
+        gc.enable()
