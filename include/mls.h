@@ -149,8 +149,9 @@ typedef struct mls_problem {
  *                    or mls_diagnostics (contents are not kept between calls).
  *                    It is the largest of three needs: the forward's two
  *                    16-byte partial records per sub-model, token and 128-row
- *                    vocabulary tile; the backward's per-chunk logit-gradient
- *                    slab (normally the largest); the
+ *                    (fp32 inputs: 64-row) vocabulary tile; the backward's
+ *                    per-chunk logit-gradient slab (normally the largest)
+ *                    and, where grad_h is taken in parts, their fp32 sums; the
  *                    diagnostics' two records of (M*M + 3M) floats per token
  *                    and 128-row vocabulary tile.
  *   stats_bytes      per-row statistics the forward writes and the backward
