@@ -13,12 +13,11 @@
 //    most probable tokens (ties: lower index first) up to and including the
 //    first one at which the kept mass reaches top_p. The nucleus threshold is
 //    the largest exp-weight value theta whose "weight >= theta" mass still
-//    reaches top_p of the total, found by bisection on the fp32 bit pattern
-//    (positive floats order like their bits); tokens tied at theta are kept in
+//    reaches top_p of the total (found as described below); tokens tied at theta are kept in
 //    index order as far as needed. A draw with uniform u returns the smallest
 //    index whose cumulative kept weight in index order exceeds u times the
 //    kept total.
-// 3. verify_kernel: one block per sequence walks its gamma drafts: the draft
+// 3. verify_kernel: one block per sequence tests its gamma drafts: the draft
 //    token x is kept when u * q(x) < p(x); at the first rejection the next
 //    token is drawn from max(0, p - q); if all are kept, one more token is drawn
 //    from the verifier's distribution after the drafts. Greedy mode compares

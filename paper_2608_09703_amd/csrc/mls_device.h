@@ -4,8 +4,9 @@
 // product C[m][n] = sum_k A[m][k] * B[n][k] where both operands are
 // row-major with the contraction index contiguous. The logits l = W h^T of
 // the LM head (paper section 2, "Modeling") are computed this way with
-// A = W_i (vocabulary rows) and B = h_i (token rows); the two backward
-// products use pre-transposed operands so that they take the same form.
+// A = W_i (vocabulary rows) and B = h_i (token rows); the general bf16 backward
+// takes its two products to the same form with transposed operands (the other
+// gradient GEMMs read theirs as stored).
 //
 // Tiles are staged through LDS in rows of 128 bytes of K (64 bf16 or 32 fp32
 // values). Each row holds eight 16-byte chunks, stored at a position XOR-ed

@@ -201,7 +201,7 @@ struct GradArgs {
 // Cross-model diagnostics (M <= kMaxDiagModels).
 constexpr int kMaxDiagModels = 4;
 constexpr int kDiagBN = 128;     // token tile, wide bf16 path
-constexpr int kDiagGenBN = 64;   // token tile, general path
+constexpr int kDiagGenBN = 64;   // token tile, fp32 path
 struct DiagArgs {
   int32_t M;
   const void* h[kMaxModels];
