@@ -4,8 +4,9 @@
 // 0.4, a smaller sub-model drafting gamma tokens and a larger one verifying).
 //
 // 1. head_logits_kernel: logits[t][v] = sum_k o[t][k] W[v][k] in fp32, on the
-//    MFMA tile core (128 or 192 vocabulary rows x 128 tokens); the fp32 tile is
-//    staged in LDS and leaves the block as 16-byte stores of token-major rows.
+//    MFMA tile core (tiles from 64 vocabulary rows x 32 tokens to 192 x 128, by
+//    the rule at head_tile); the fp32 tile is staged in LDS and leaves the block
+//    as 16-byte stores of token-major rows.
 //    Decode batches are small, so the [rows, V] logits are cheap next to the
 //    head itself.
 // 2. sample_kernel: one 1024-thread block per row. The row's sampling
