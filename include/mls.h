@@ -342,7 +342,8 @@ mls_status mls_head_logits(int64_t T, int64_t V, int64_t d, int32_t dtype, const
  * uniform u[r] (device [rows]; may be NULL when greedy). When params is not
  * NULL (and not greedy), row r's distribution record is also written to
  * params + r * MLS_ROW_PARAMS_BYTES (device, 4-byte aligned): a drafting loop
- * can hand these records to mls_spec_verify as draft_params.
+ * can hand these records to mls_spec_verify as draft_params. A row that keeps
+ * no token when sampled (one with a +inf logit, or of NaN or -inf only) gives -1.
  */
 mls_status mls_sample(const mls_sampling* s, int64_t rows, const float* logits, const float* u,
                       int32_t* tokens, void* params, void* stream);
@@ -371,7 +372,9 @@ mls_status mls_spec_verify_workspace(int64_t batch, int64_t gamma, size_t* bytes
  * draft_params (device, may be NULL): [gamma][batch] records of
  * MLS_ROW_PARAMS_BYTES from mls_sample on the same draft rows with the same
  * sampling settings; then the draft rows' distributions are not recomputed.
- * Outputs n_accepted, next_token: int32 [batch]. Asynchronous on stream.
+ * Outputs n_accepted, next_token: int32 [batch]; next_token is -1 where it is
+ * to be drawn from a verifier row that keeps no token (see mls_sample).
+ * Asynchronous on stream.
  */
 mls_status mls_spec_verify(const mls_sampling* s, int64_t batch, int64_t gamma,
                            const float* draft_logits, const float* target_logits,

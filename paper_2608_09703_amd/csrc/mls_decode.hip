@@ -961,11 +961,13 @@ __device__ __forceinline__ int compact_kept(const float* prow, int V, float it, 
 
 // List wave: a draw from p's kept list (n entries) with uniform u; with a
 // draft row qrow (parameters dq), from max(0, p - q), or p itself if that has
-// no mass.
+// no mass. -1 where p keeps no token (a row with a +inf logit, or of NaN or -inf
+// only), as the sampler gives for such a row.
 template <int RUN>
 __device__ __forceinline__ int list_residual_draw(const RowShared& sh, int n, const RowDist& dp,
                                                   const float* qrow, const RowDist& dq, float it,
                                                   float u) {
+  if (n == 0) return -1;
   float w[RUN];
   load_run<RUN>(sh, n, w);
   if (qrow) {

@@ -401,3 +401,25 @@ def test_draft_params_from_the_sampler():
     z = (dls.float().cpu() * (1 / 0.4)).max(dim=2).values
     assert torch.allclose(f[:, :, 0], z, rtol=1e-6)
     assert bool(((f[:, :, 4] > 0) & (f[:, :, 4] <= f[:, :, 1] * (1 + 1e-6))).all())
+
+
+@pytest.mark.parametrize("V", [777, 49152])
+def test_rows_without_a_kept_token_give_minus_one(V):
+    """A verifier row with a +inf logit (its own weight is NaN, the others are 0), of
+    NaN or of -inf alone keeps no token: the draw after a rejection and the one after
+    the last draft are -1, as the sampler's own draw from such a row is."""
+    bad = torch.randn(3, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV)
+    bad[0, V // 2] = float("inf")
+    bad[1] = float("nan")
+    bad[2] = float("-inf")
+    u = torch.tensor([0.1, 0.5, 0.9], device=DEV)
+    for top_p in (0.9, 1.0):
+        assert D.sample(bad, u, temperature=0.7, top_p=top_p).tolist() == [-1] * 3
+        n, x = D.spec_verify(None, bad[:, None].contiguous(), None, None, u, temperature=0.7,
+                             top_p=top_p)
+        assert n.tolist() == [0] * 3 and x.tolist() == [-1] * 3
+        good = torch.zeros(1, 3, V, device=DEV)
+        n, x = D.spec_verify(good, bad[:, None].repeat(1, 2, 1).contiguous(),
+                             torch.zeros(1, 3, dtype=torch.int32, device=DEV), u[None].contiguous(),
+                             u, temperature=0.7, top_p=top_p)
+        assert n.tolist() == [0] * 3 and x.tolist() == [-1] * 3
