@@ -343,7 +343,8 @@ mls_status mls_head_logits(int64_t T, int64_t V, int64_t d, int32_t dtype, const
  * NULL (and not greedy), row r's distribution record is also written to
  * params + r * MLS_ROW_PARAMS_BYTES (device, 4-byte aligned): a drafting loop
  * can hand these records to mls_spec_verify as draft_params. A row that keeps
- * no token when sampled (one with a +inf logit, or of NaN or -inf only) gives -1.
+ * no token when sampled (one with a +inf logit, or of NaN or -inf only) gives -1,
+ * as does a greedy row without a logit above -inf.
  */
 mls_status mls_sample(const mls_sampling* s, int64_t rows, const float* logits, const float* u,
                       int32_t* tokens, void* params, void* stream);

@@ -841,7 +841,7 @@ __device__ __forceinline__ int row_argmax(const float* row, int V, RowShared& sh
   }
   bi = bi == 0x7fffffff ? bi : elem_v<EPT>(0) + 64 * bi;
   block_argmax(best, bi, sh);
-  return bi;
+  return bi == 0x7fffffff ? -1 : bi;  // no logit above -inf: no token
 }
 
 // The distribution from the list (list wave), then (with u >= 0) a draw;

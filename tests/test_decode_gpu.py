@@ -423,3 +423,18 @@ def test_rows_without_a_kept_token_give_minus_one(V):
                              torch.zeros(1, 3, dtype=torch.int32, device=DEV), u[None].contiguous(),
                              u, temperature=0.7, top_p=top_p)
         assert n.tolist() == [0] * 3 and x.tolist() == [-1] * 3
+
+
+def test_greedy_rows_without_a_maximum_give_minus_one():
+    """Greedy rows of NaN or of -inf alone have no argmax: -1, in the sampler and as the
+    verifier's token; a +inf logit and finite logits beside NaN are found as usual."""
+    V = 1500
+    rows = torch.full((4, V), float("nan"), device=DEV)
+    rows[1] = float("-inf")
+    rows[2] = 0.0
+    rows[2, 700] = float("inf")
+    rows[3, 1400] = -2.0
+    want = [-1, -1, 700, 1400]
+    assert D.sample(rows, None, greedy=True).tolist() == want
+    n, x = D.spec_verify(None, rows[:, None].contiguous(), None, None, None, greedy=True)
+    assert n.tolist() == [0] * 4 and x.tolist() == want
