@@ -127,7 +127,9 @@ struct Plan {
   bool grad_h_bf16 = false;
   size_t off_slab = 0, off_slabT = 0, off_hT = 0, off_WT = 0, off_ghp = 0, bwd_bytes = 0;
   // K parts of the wide grad_h products (1: none), each of *_ks elements of K,
-  // with fp32 partial outputs at off_ghp / fb_off_ghp
+  // with fp32 partial outputs at off_ghp / fb_off_ghp; set by plan_bwd_parts /
+  // plan_fb_parts for the calls that take them and for the size queries only
+  // (the search takes some microseconds of every call otherwise)
   int bwd_splits = 1, fb_splits = 1;
   int64_t bwd_ks = 0, fb_ks = 0;
   size_t fb_off_ghp = 0;
@@ -298,12 +300,9 @@ void make_plan(const mls_problem* p, Plan& pl) {
     pl.off_WT = off;
     off = align256(off + (size_t)pl.sumd * pl.Vc * pl.es);
   }
-  if (pl.wide_bwd)
-    grad_h_parts(p, pl.T, std::min(pl.Vc, pl.V), &pl.bwd_splits, &pl.bwd_ks);
-  if ((pl.grad_h_bf16 && pl.n_chunks > 1) || pl.bwd_splits > 1) {
-    pl.off_ghp = off;
-    off = align256(off + (size_t)pl.bwd_splits * pl.sumd * pl.T * sizeof(float));
-  }
+  pl.off_ghp = off;
+  if (pl.grad_h_bf16 && pl.n_chunks > 1)
+    off = align256(off + (size_t)pl.sumd * pl.T * sizeof(float));
   pl.bwd_bytes = off;
 
   // diagnostics: one record per (vocabulary tile, token) of the sub-models of
@@ -357,11 +356,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
     off = align256(off + (size_t)rec_per_tok * pl.fb_tc);
     pl.fb_off_lab = off;
     off = align256(off + (size_t)pl.M * pl.T * sizeof(float));
-    grad_h_parts(p, pl.fb_tc, pl.V, &pl.fb_splits, &pl.fb_ks);
-    if (pl.fb_splits > 1) {
-      pl.fb_off_ghp = off;
-      off = align256(off + (size_t)pl.fb_splits * pl.sumd * pl.fb_tc * sizeof(float));
-    }
+    pl.fb_off_ghp = off;
     pl.fb_bytes = off;
   } else {
     pl.fb_bytes = std::max(pl.fwd_bytes, pl.bwd_bytes);
@@ -369,6 +364,23 @@ void make_plan(const mls_problem* p, Plan& pl) {
 
   pl.header_off = (size_t)(4ll * pl.M * pl.T + pl.T) * sizeof(float);
   pl.stats_bytes = align256(pl.header_off + 2 * sizeof(int32_t));
+}
+
+// K parts of the backward's grad_h products and their room behind the slab.
+void plan_bwd_parts(const mls_problem* p, Plan& pl) {
+  if (!pl.wide_bwd) return;
+  grad_h_parts(p, pl.T, std::min(pl.Vc, pl.V), &pl.bwd_splits, &pl.bwd_ks);
+  if (pl.bwd_splits > 1)
+    pl.bwd_bytes = align256(pl.off_ghp + (size_t)pl.bwd_splits * pl.sumd * pl.T * sizeof(float));
+  pl.ws_bytes = std::max(pl.ws_bytes, pl.bwd_bytes);
+  if (!pl.fb_store) pl.fb_bytes = std::max(pl.fb_bytes, pl.bwd_bytes);
+}
+
+// The same for the stored-logit forward + backward.
+void plan_fb_parts(const mls_problem* p, Plan& pl) {
+  grad_h_parts(p, pl.fb_tc, pl.V, &pl.fb_splits, &pl.fb_ks);
+  if (pl.fb_splits > 1)
+    pl.fb_bytes = align256(pl.fb_off_ghp + (size_t)pl.fb_splits * pl.sumd * pl.fb_tc * sizeof(float));
 }
 
 void fill_order(const Plan& pl, int32_t* order) {
@@ -599,6 +611,7 @@ mls_status mls_query_sizes(const mls_problem* p, size_t* workspace_bytes, size_t
   if (st != MLS_OK) return st;
   Plan pl;
   make_plan(p, pl);
+  plan_bwd_parts(p, pl);
   if (workspace_bytes) *workspace_bytes = pl.ws_bytes;
   if (stats_bytes) *stats_bytes = pl.stats_bytes;
   return MLS_OK;
@@ -667,6 +680,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
   }
   Plan pl;
   make_plan(p, pl);
+  plan_bwd_parts(p, pl);
   if (workspace_bytes < pl.bwd_bytes)
     return fail(MLS_WORKSPACE_TOO_SMALL, "backward needs %zu workspace bytes, got %zu", pl.bwd_bytes,
                 workspace_bytes);
@@ -901,6 +915,10 @@ mls_status mls_query_fwd_bwd_workspace(const mls_problem* p, size_t* workspace_b
   if (!workspace_bytes) return fail(MLS_INVALID_ARG, "workspace_bytes is NULL");
   Plan pl;
   make_plan(p, pl);
+  if (pl.fb_store)
+    plan_fb_parts(p, pl);
+  else
+    plan_bwd_parts(p, pl);
   *workspace_bytes = pl.fb_bytes;
   return MLS_OK;
 }
@@ -927,6 +945,10 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
   }
   Plan pl;
   make_plan(p, pl);
+  if (pl.fb_store)
+    plan_fb_parts(p, pl);
+  else
+    plan_bwd_parts(p, pl);
   if (workspace_bytes < pl.fb_bytes)
     return fail(MLS_WORKSPACE_TOO_SMALL, "forward + backward needs %zu workspace bytes, got %zu",
                 pl.fb_bytes, workspace_bytes);
