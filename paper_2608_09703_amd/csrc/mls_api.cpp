@@ -465,7 +465,9 @@ int f32_gemm_tile(const Plan& pl, const mls_problem* p) {
 }
 
 // grad_h rows [t0, t0 + rows) of every sub-model from their K parts, which lie
-// one sub-model after the other ([splits][rows][d_i] each).
+// one sub-model after the other ([splits][rows][d_i] each). Nothing is launched
+// where no grad_h is asked for. (The number of parts does not depend on which
+// outputs are, so that a gradient's bits do not.)
 hipError_t sum_parts(const mls_problem* p, int splits, int64_t rows, const float* part,
                      void* const* grad_h, int64_t t0, hipStream_t s) {
   SplitSumArgs a;
@@ -475,12 +477,15 @@ hipError_t sum_parts(const mls_problem* p, int splits, int64_t rows, const float
   a.accumulate = (p->flags & MLS_ACCUMULATE_GRAD_H) ? 1 : 0;
   a.out16 = p->grad_h_dtype == MLS_BF16 ? 1 : 0;
   const size_t es = a.out16 ? 2 : 4;
+  bool any = false;
   for (int i = 0; i < p->M; ++i) {
+    any = any || grad_h[i];
     a.part[i] = part;
     a.n[i] = rows * p->d[i];
     a.out[i] = grad_h[i] ? static_cast<char*>(grad_h[i]) + (size_t)t0 * p->d[i] * es : nullptr;
     part += a.n[i] * splits;
   }
+  if (!any) return hipSuccess;
   ProfScope ps("split_sum", s);
   return launch_split_sum(a, s);
 }

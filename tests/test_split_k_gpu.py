@@ -61,3 +61,36 @@ def test_k_parts_accumulate_and_skip(dt):
     D.backward(p, buf, dev, c[0], c[1], [None, out], [None, None])
     want = (torch.tensor(base["grad_h"][1], device=DEV) + 0.5).to(dt)
     assert torch.equal(out, want)
+
+
+def test_no_sum_without_a_hidden_state_gradient():
+    """The sum over the parts is launched with the gradients it is for, in both plans, and only then;
+    the head gradients are the same bits either way."""
+    wl = WL.custom(2, 150, (64, 128), 9000, w_std=0.1, seed=65)
+    h, W, y = WL.make_inputs(wl, device=DEV)
+    dev = torch.device(DEV)
+    p = D.make_problem(h, W, y)
+    buf = D.Buffers(p, dev)
+    c = [torch.tensor(v, device=DEV) for v in ([1.0, 1.0], [0.5, 0.0])]
+    ws = torch.empty(B.query_fwd_bwd_workspace(p), dtype=torch.uint8, device=DEV)
+    gh = [torch.empty(x.shape, device=DEV) for x in h]
+    D.forward(p, buf, dev)
+    for fused in (False, True):
+        got = {}
+        for want_h in (True, False):
+            gW = [torch.empty(x.shape, device=DEV) for x in W]
+            outs = gh if want_h else [None, None]
+            B.profile_enable(True)
+            try:
+                if fused:
+                    B.distill_fwd_bwd(p, buf.stats.data_ptr(), buf.ce.data_ptr(), buf.kl.data_ptr(), None,
+                                      c[0].data_ptr(), c[1].data_ptr(),
+                                      [x.data_ptr() if x is not None else None for x in outs],
+                                      [x.data_ptr() for x in gW], ws.data_ptr(), ws.numel(), D._stream(dev))
+                else:
+                    D.backward(p, buf, dev, c[0], c[1], outs, gW)
+                assert ("split_sum" in B.profile_report()) == want_h, (fused, want_h)
+            finally:
+                B.profile_enable(False)
+            got[want_h] = gW
+        assert all(torch.equal(a, b) for a, b in zip(got[True], got[False]))
