@@ -151,9 +151,14 @@ typedef struct mls_problem {
  *                    16-byte partial records per sub-model, token and 128-row
  *                    (fp32 inputs: 64-row) vocabulary tile; the backward's
  *                    per-chunk logit-gradient slab (normally the largest)
- *                    and, where grad_h is taken in parts, their fp32 sums; the
+ *                    and room for fp32 sums of grad_h taken in parts; the
  *                    diagnostics' two records of (M*M + 3M) floats per token
- *                    and 128-row vocabulary tile.
+ *                    and 128-row vocabulary tile. The room for the parts (at
+ *                    most 128 MiB) is reported such that a size queried for
+ *                    some T suffices for every smaller T of the same problem.
+ *                    It is not required: each call accepts any workspace that
+ *                    holds the rest, and takes as many parts as fit, which
+ *                    changes its speed and the order of grad_h's fp32 sums.
  *   stats_bytes      per-row statistics the forward writes and the backward
  *                    reads. Layout (all little-endian, offsets in elements of
  *                    float32 from the start):
@@ -224,8 +229,8 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
  * 4 GiB or all of them 16 GiB. Problems of one 128-token tile, widths that are
  * not multiples of 64, fp32 inputs, heads [V, d_i] of 4 GiB or more, or
  * MLS_FWD_BWD_RECOMPUTE in p->flags run the forward and then the recomputing
- * backward instead. workspace_bytes: at least what mls_query_fwd_bwd_workspace
- * reports. Asynchronous on stream.
+ * backward instead. workspace_bytes: as mls_query_fwd_bwd_workspace reports
+ * (room for grad_h parts included, see mls_query_sizes). Asynchronous on stream.
  */
 mls_status mls_query_fwd_bwd_workspace(const mls_problem* p, size_t* workspace_bytes);
 mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, float* kl,

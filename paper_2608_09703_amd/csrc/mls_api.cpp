@@ -89,6 +89,8 @@ constexpr int64_t kLogitSlabBudget = 16ll << 30;  // stored logits of one token 
 constexpr int64_t kPanelMax = (1ll << 32) - 1;    // bytes one wide-GEMM operand may span
 constexpr int64_t kCus = 256;                     // compute units of the part
 constexpr int64_t kMaxSplits = 16;                // K parts of a grad_h product
+constexpr int64_t kPartTiles = 192;               // grad_h tiles of a launch that still takes K parts
+constexpr int64_t kPartBytes = 128ll << 20;       // fp32 outputs of all parts
 
 struct Plan {
   int M = 0;
@@ -126,18 +128,15 @@ struct Plan {
   // backward workspace (off_ghp: fp32 partial sums of a bf16 grad_h over vocabulary chunks)
   bool grad_h_bf16 = false;
   size_t off_slab = 0, off_slabT = 0, off_hT = 0, off_WT = 0, off_ghp = 0, bwd_bytes = 0;
-  // K parts of the wide grad_h products (1: none), each of *_ks elements of K,
-  // with fp32 partial outputs at off_ghp / fb_off_ghp; set by plan_bwd_parts /
-  // plan_fb_parts for the calls that take them and for the size queries only
-  // (the search takes some microseconds of every call otherwise)
-  int bwd_splits = 1, fb_splits = 1;
-  int64_t bwd_ks = 0, fb_ks = 0;
-  size_t fb_off_ghp = 0;
+  // K parts of the wide grad_h products have their fp32 outputs at off_ghp /
+  // fb_off_ghp, in what the workspace holds beyond them: *_bytes is what a call
+  // cannot do without, *_room what the size queries report
+  size_t fb_off_ghp = 0, bwd_room = 0, fb_room = 0;
   // diagnostics workspace (vocabulary segments of the pairwise pass)
   int n_vt_diag = 0, n_tt_diag = 0;
   int m_diag = 0;  // sub-models per diagnostics pass (at most kMaxDiagModels)
   size_t off_dpart = 0, off_drow = 0, off_dsub = 0, off_dam = 0, diag_bytes = 0;
-  size_t ws_bytes = 0;
+  size_t ws_room = 0;
   size_t stats_bytes = 0;
   size_t header_off = 0;
 };
@@ -159,35 +158,54 @@ int64_t launch_span(int64_t n1, int64_t c1, int64_t n2, int64_t c2) {
   return lo;
 }
 
+// Output tiles of 256 columns of one row block of every grad_h.
+int64_t grad_h_cols(const mls_problem* p) {
+  int64_t cols = 0;
+  for (int i = 0; i < p->M; ++i) cols += (p->d[i] + gemm_tile_cols(true) - 1) / gemm_tile_cols(true);
+  return cols;
+}
+
+// The most K parts for vrows of K: 16 K-tiles or more each.
+int64_t max_parts(int64_t vrows) {
+  const int64_t bk = gemm_wide_k_tile();
+  return std::min(kMaxSplits, (vrows + bk - 1) / bk / 16);
+}
+
 // K parts of the grad_h products of one launch of the wide gradient GEMM over
-// `rows` tokens and `vrows` vocabulary rows, and the K extent of a part. A
-// grad_h tile runs over all of vrows, a grad_W tile over the tokens only, so
-// with few tokens the launch has few, long grad_h tiles and lasts as long as one
-// of them while most CUs are done. K is cut into as many parts (at most
-// kMaxSplits) as give the shortest launch by a count of K-tiles per CU, a tile's
-// prologue and output counted as 3 and the sum over the parts at 5 TB/s; not
-// for less than 4 %. Forward + backward at T = 512, widths 1,024 / 2,048 /
-// 3,072, V = 50,304: 3,268 -> 1,768 us; T = 1,024, widths 512 / 1,024, V =
-// 32,000: 1,502 -> 530 us. With 4,096 tokens of the headline shape one part
+// `rows` tokens and `vrows` vocabulary rows, whose fp32 outputs fit `room`
+// bytes, and the K extent of a part. A grad_h tile runs over all of vrows, a
+// grad_W tile over the tokens only, so with few tokens the launch has few, long
+// grad_h tiles and lasts as long as one of them while most CUs are done. K is
+// cut into as many parts (at most kMaxSplits) as give the shortest launch by a
+// count of K-tiles per CU, a tile's prologue and output counted as 6 and the sum
+// over the parts at 5 TB/s; not for less than 4 %. Above kPartTiles tiles few CUs
+// idle and parts pay little or nothing: at 196, two parts against one take 1,321
+// and 1,361 us (backward, T = 6,967, widths 256 / 1,344, V = 15,360), 4,894-5,140
+// and 4,815-4,828 us (T = 6,990, widths 320 / 384 / 704, V = 64,512). Forward +
+// backward in one call, before there were parts (and with a main loop 3 % slower)
+// and with them: T = 512, widths 1,024 / 2,048 / 3,072, V = 50,304: 3,273 ->
+// 1,829 us; T = 1,024, widths 512 / 1,024, V = 32,000: 1,394 -> 483 us. With 4,096 tokens of the headline shape one part
 // remains the shortest.
-void grad_h_parts(const mls_problem* p, int64_t rows, int64_t vrows, int* splits, int64_t* ksplit) {
+void grad_h_parts(const mls_problem* p, int64_t rows, int64_t vrows, size_t room, int* splits,
+                  int64_t* ksplit) {
   constexpr int64_t kTileCost = 6;       // K-tiles
   constexpr int64_t kTileBytes = 4 << 20;  // bytes at 5 TB/s in a K-tile's 0.8 us
-  const int64_t bm = gemm_tile_rows(true), bn = gemm_tile_cols(true), bk = gemm_wide_k_tile();
+  const int64_t bm = gemm_tile_rows(true), bk = gemm_wide_k_tile();
   const int64_t nk = (vrows + bk - 1) / bk, nkw = (rows + bk - 1) / bk;
-  int64_t cols = 0, sumd = 0;
-  for (int i = 0; i < p->M; ++i) {
-    cols += (p->d[i] + bn - 1) / bn;
-    sumd += p->d[i];
-  }
+  const int64_t cols = grad_h_cols(p);
+  int64_t sumd = 0;
+  for (int i = 0; i < p->M; ++i) sumd += p->d[i];
   const int64_t n1 = (rows + bm - 1) / bm * cols, n2 = (vrows + bm - 1) / bm * cols;
+  const int64_t most = std::min<int64_t>(room, kPartBytes) / (rows * sumd * 4);
   *splits = 1;
   *ksplit = nk * bk;
+  if (n1 > kPartTiles || most < 2) return;
   int64_t best = launch_span(n1, nk + kTileCost, n2, nkw + kTileCost);
   best -= best / 25;
-  for (int64_t want = 2; want <= kMaxSplits && nk / want >= 16; ++want) {
+  for (int64_t want = 2; want <= max_parts(vrows); ++want) {
     const int64_t per = (nk + want - 1) / want;
     const int64_t s = (nk + per - 1) / per;
+    if (s > most) break;
     const int64_t t = launch_span(n1 * s, per + kTileCost, n2, nkw + kTileCost) +
                       2 * s * rows * sumd * 4 / kTileBytes;
     if (t < best) {
@@ -230,6 +248,32 @@ mls_status validate(const mls_problem* p) {
   return MLS_OK;
 }
 
+// Vocabulary rows of a backward chunk at T_pad tokens, before the caps of the
+// wide path.
+int64_t chunk_rows(const mls_problem* p, const Plan& pl, int64_t T_pad) {
+  int64_t vc;
+  if (p->vocab_chunk > 0) {
+    vc = round_up(p->vocab_chunk, 256);
+  } else {
+    // At least kMinChunks balanced chunks, more when the slabs of one chunk
+    // would exceed kSlabTargetBytes (the wide path keeps one slab layout, the
+    // general path two), so the logit-gradient slab never spans the whole
+    // vocabulary (V > 256).
+    const int64_t per_row = (pl.wide_bwd && !pl.ktail ? 1ll : 2ll) * pl.M * T_pad * pl.es;
+    const int64_t fit = std::max<int64_t>(256, kSlabTargetBytes / per_row / 256 * 256);
+    const int64_t n = std::max<int64_t>(kMinChunks, (p->V + fit - 1) / fit);
+    vc = round_up((p->V + n - 1) / n, 256);
+  }
+  return std::min(vc, round_up(p->V, 256));
+}
+
+// Bytes of the parts' outputs a workspace is reported with, for rows of tokens
+// and vrows of K.
+size_t parts_room(const Plan& pl, int64_t rows, int64_t vrows) {
+  const int64_t n = max_parts(vrows);
+  return n < 2 ? 0 : align256((size_t)std::min(kPartBytes, n * rows * pl.sumd * 4));
+}
+
 void make_plan(const mls_problem* p, Plan& pl) {
   pl.M = p->M;
   pl.s = p->teacher < 0 ? p->M - 1 : p->teacher;
@@ -248,20 +292,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
   int64_t dmax = 0;
   for (int i = 0; i < p->M; ++i) dmax = std::max<int64_t>(dmax, p->d[i]);
   pl.wide_bwd = pl.wide && pl.T_pad * dmax * pl.es <= kPanelMax && pl.T_pad * 256 * pl.es <= kPanelMax;
-  const int64_t vmax = round_up(p->V, 256);
-  int64_t vc;
-  if (p->vocab_chunk > 0) {
-    vc = round_up(p->vocab_chunk, 256);
-  } else {
-    // At least kMinChunks balanced chunks, more when the slabs of one chunk
-    // would exceed kSlabTargetBytes (the wide path keeps one slab layout, the
-    // general path two), so the logit-gradient slab never spans the whole
-    // vocabulary (V > 256).
-    const int64_t per_row = (pl.wide_bwd && !pl.ktail ? 1ll : 2ll) * pl.M * pl.T_pad * pl.es;
-    const int64_t fit = std::max<int64_t>(256, kSlabTargetBytes / per_row / 256 * 256);
-    const int64_t n = std::max<int64_t>(kMinChunks, (p->V + fit - 1) / fit);
-    vc = round_up((p->V + n - 1) / n, 256);
-  }
+  int64_t vc = chunk_rows(p, pl, pl.T_pad);
   if (pl.wide_bwd) {
     // one slab [T_pad][Vc] and one head chunk [Vc][d_i] below 4 GiB each
     const int64_t cap = std::min(kPanelMax / (pl.T_pad * pl.es), kPanelMax / (dmax * pl.es)) / 256 * 256;
@@ -269,10 +300,10 @@ void make_plan(const mls_problem* p, Plan& pl) {
     // a wider one goes to the general kernels
     if (!pl.ktail)
       vc = std::min(vc, cap);
-    else if (std::min(vc, vmax) > cap)
+    else if (vc > cap)
       pl.wide_bwd = false;
   }
-  pl.Vc = std::max<int64_t>(256, std::min(vc, vmax));
+  pl.Vc = std::max<int64_t>(256, vc);
   pl.n_chunks = (int)((p->V + pl.Vc - 1) / pl.Vc);
   pl.grad_h_bf16 = p->grad_h_dtype == MLS_BF16;
 
@@ -304,6 +335,17 @@ void make_plan(const mls_problem* p, Plan& pl) {
   if (pl.grad_h_bf16 && pl.n_chunks > 1)
     off = align256(off + (size_t)pl.sumd * pl.T * sizeof(float));
   pl.bwd_bytes = off;
+  // Reported: room for the K parts at every number of tokens up to this one, so
+  // that a workspace sized for the longest batch serves the shorter ones (the
+  // parts need most where tokens are few: none above part_rows).
+  const int64_t part_rows = gemm_tile_rows(true) * (kPartTiles / grad_h_cols(p));
+  pl.bwd_room = pl.bwd_bytes;
+  if (pl.wide_bwd && part_rows > 0) {
+    const int64_t rows = std::min(pl.T, part_rows), pad = round_up(rows, kFusedBN);
+    const int64_t vr = rows < pl.T ? chunk_rows(p, pl, pad) : pl.Vc;
+    pl.bwd_room = std::max(pl.bwd_room, align256((size_t)pl.M * pad * vr * pl.es) +
+                                            parts_room(pl, rows, std::min(vr, pl.V)));
+  }
 
   // diagnostics: one record per (vocabulary tile, token) of the sub-models of
   // one pass; suites of more than kMaxDiagModels run several passes over
@@ -327,7 +369,7 @@ void make_plan(const mls_problem* p, Plan& pl) {
     }
     pl.diag_bytes = off;
   }
-  pl.ws_bytes = std::max(std::max(pl.fwd_bytes, pl.bwd_bytes), pl.diag_bytes);
+  pl.ws_room = std::max(std::max(pl.fwd_bytes, pl.bwd_room), pl.diag_bytes);
 
   // fused forward + backward with stored logits: at least two token chunks (so
   // no [T, V] logits exist), each sub-model's fp16 slab below 4 GiB (the wide
@@ -358,29 +400,21 @@ void make_plan(const mls_problem* p, Plan& pl) {
     off = align256(off + (size_t)pl.M * pl.T * sizeof(float));
     pl.fb_off_ghp = off;
     pl.fb_bytes = off;
+    pl.fb_room = off;
+    if (part_rows > 0) {  // as bwd_room
+      const int64_t rows = std::min(pl.fb_tc, part_rows);
+      pl.fb_room = std::max(pl.fb_room, align256((size_t)pl.M * rows * pl.fb_ld * 2) +
+                                            align256((size_t)rec_per_tok * rows) +
+                                            align256((size_t)pl.M * pl.T * sizeof(float)) +
+                                            parts_room(pl, rows, pl.V));
+    }
   } else {
     pl.fb_bytes = std::max(pl.fwd_bytes, pl.bwd_bytes);
+    pl.fb_room = std::max(pl.fwd_bytes, pl.bwd_room);
   }
 
   pl.header_off = (size_t)(4ll * pl.M * pl.T + pl.T) * sizeof(float);
   pl.stats_bytes = align256(pl.header_off + 2 * sizeof(int32_t));
-}
-
-// K parts of the backward's grad_h products and their room behind the slab.
-void plan_bwd_parts(const mls_problem* p, Plan& pl) {
-  if (!pl.wide_bwd) return;
-  grad_h_parts(p, pl.T, std::min(pl.Vc, pl.V), &pl.bwd_splits, &pl.bwd_ks);
-  if (pl.bwd_splits > 1)
-    pl.bwd_bytes = align256(pl.off_ghp + (size_t)pl.bwd_splits * pl.sumd * pl.T * sizeof(float));
-  pl.ws_bytes = std::max(pl.ws_bytes, pl.bwd_bytes);
-  if (!pl.fb_store) pl.fb_bytes = std::max(pl.fb_bytes, pl.bwd_bytes);
-}
-
-// The same for the stored-logit forward + backward.
-void plan_fb_parts(const mls_problem* p, Plan& pl) {
-  grad_h_parts(p, pl.fb_tc, pl.V, &pl.fb_splits, &pl.fb_ks);
-  if (pl.fb_splits > 1)
-    pl.fb_bytes = align256(pl.fb_off_ghp + (size_t)pl.fb_splits * pl.sumd * pl.fb_tc * sizeof(float));
 }
 
 void fill_order(const Plan& pl, int32_t* order) {
@@ -616,8 +650,7 @@ mls_status mls_query_sizes(const mls_problem* p, size_t* workspace_bytes, size_t
   if (st != MLS_OK) return st;
   Plan pl;
   make_plan(p, pl);
-  plan_bwd_parts(p, pl);
-  if (workspace_bytes) *workspace_bytes = pl.ws_bytes;
+  if (workspace_bytes) *workspace_bytes = pl.ws_room;
   if (stats_bytes) *stats_bytes = pl.stats_bytes;
   return MLS_OK;
 }
@@ -685,10 +718,13 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
   }
   Plan pl;
   make_plan(p, pl);
-  plan_bwd_parts(p, pl);
   if (workspace_bytes < pl.bwd_bytes)
     return fail(MLS_WORKSPACE_TOO_SMALL, "backward needs %zu workspace bytes, got %zu", pl.bwd_bytes,
                 workspace_bytes);
+  int splits = 1;  // K parts of the grad_h products
+  int64_t ksplit = 0;
+  if (pl.wide_bwd)
+    grad_h_parts(p, pl.T, std::min(pl.Vc, pl.V), workspace_bytes - pl.off_ghp, &splits, &ksplit);
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   const float* sf = static_cast<const float*>(stats);
@@ -816,10 +852,10 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       // partial sums of the earlier chunks in fp32 and is stored once, by the last
       const bool last = c == pl.n_chunks - 1;
       const bool acc_flag = (p->flags & MLS_ACCUMULATE_GRAD_H) != 0;
-      float* ghp = (pl.grad_h_bf16 && pl.n_chunks > 1) || pl.bwd_splits > 1
-                       ? reinterpret_cast<float*>(ws + pl.off_ghp) + doff[i] * pl.T * pl.bwd_splits
+      float* ghp = (pl.grad_h_bf16 && pl.n_chunks > 1) || splits > 1
+                       ? reinterpret_cast<float*>(ws + pl.off_ghp) + doff[i] * pl.T * splits
                        : nullptr;
-      if (pl.bwd_splits > 1) {  // parts accumulate over the chunks, added up at the end
+      if (splits > 1) {  // parts accumulate over the chunks, added up at the end
         g.C = ghp;
         g.accumulate = c > 0 ? 1 : 0;
       } else if (!pl.grad_h_bf16) {
@@ -844,8 +880,8 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       g.tiles_n = (int)((p->d[i] + tbn - 1) / tbn);
       g.tile_begin = tiles;
       g.group_m = 8;
-      if (pl.bwd_splits > 1) {
-        g.ksplit = pl.bwd_ks;
+      if (splits > 1) {
+        g.ksplit = ksplit;
         g.splits = (int)((g.K + g.ksplit - 1) / g.ksplit);  // fewer in a shorter last chunk
         g.csplit = pl.T * p->d[i];
       }
@@ -906,8 +942,8 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
     }
     if (e != hipSuccess) return hip_fail(e, "gradient GEMM launch");
   }
-  if (pl.bwd_splits > 1) {
-    e = sum_parts(p, pl.bwd_splits, pl.T, reinterpret_cast<const float*>(ws + pl.off_ghp), grad_h, 0, s);
+  if (splits > 1) {
+    e = sum_parts(p, splits, pl.T, reinterpret_cast<const float*>(ws + pl.off_ghp), grad_h, 0, s);
     if (e != hipSuccess) return hip_fail(e, "grad_h sum launch");
   }
   return MLS_OK;
@@ -920,11 +956,7 @@ mls_status mls_query_fwd_bwd_workspace(const mls_problem* p, size_t* workspace_b
   if (!workspace_bytes) return fail(MLS_INVALID_ARG, "workspace_bytes is NULL");
   Plan pl;
   make_plan(p, pl);
-  if (pl.fb_store)
-    plan_fb_parts(p, pl);
-  else
-    plan_bwd_parts(p, pl);
-  *workspace_bytes = pl.fb_bytes;
+  *workspace_bytes = pl.fb_room;
   return MLS_OK;
 }
 
@@ -950,10 +982,6 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
   }
   Plan pl;
   make_plan(p, pl);
-  if (pl.fb_store)
-    plan_fb_parts(p, pl);
-  else
-    plan_bwd_parts(p, pl);
   if (workspace_bytes < pl.fb_bytes)
     return fail(MLS_WORKSPACE_TOO_SMALL, "forward + backward needs %zu workspace bytes, got %zu",
                 pl.fb_bytes, workspace_bytes);
@@ -963,6 +991,9 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
     if (st != MLS_OK) return st;
     return mls_distill_bwd(p, stats, g_ce, g_kl, grad_h, grad_W, workspace, workspace_bytes, stream);
   }
+  int splits;  // K parts of the grad_h products
+  int64_t ksplit;
+  grad_h_parts(p, pl.fb_tc, pl.V, workspace_bytes - pl.fb_off_ghp, &splits, &ksplit);
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   float* lab = reinterpret_cast<float*>(ws + pl.fb_off_lab);
@@ -1031,17 +1062,17 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
       g.B = p->W[i];  // [v][d]
       g.ldb = p->d[i];
       g.cols = pl.V;
-      if (pl.fb_splits > 1) {
-        g.C = reinterpret_cast<float*>(ws + pl.fb_off_ghp) + doff[i] * tc * pl.fb_splits;
-        g.splits = pl.fb_splits;
-        g.ksplit = pl.fb_ks;
+      if (splits > 1) {
+        g.C = reinterpret_cast<float*>(ws + pl.fb_off_ghp) + doff[i] * tc * splits;
+        g.splits = splits;
+        g.ksplit = ksplit;
         g.csplit = tc * p->d[i];
       } else if (pl.grad_h_bf16) {
         g.Cb = static_cast<uint16_t*>(grad_h[i]) + t0 * p->d[i];
       } else {
         g.C = static_cast<float*>(grad_h[i]) + t0 * p->d[i];
       }
-      g.accumulate = pl.fb_splits == 1 && (p->flags & MLS_ACCUMULATE_GRAD_H) ? 1 : 0;
+      g.accumulate = splits == 1 && (p->flags & MLS_ACCUMULATE_GRAD_H) ? 1 : 0;
       g.ldc = p->d[i];
       g.ldc_rows = tc;
       g.K = round_up(pl.V, kt);
@@ -1088,8 +1119,8 @@ mls_status mls_distill_fwd_bwd(const mls_problem* p, void* stats, float* ce, flo
       e = launch_gemm_wide(gm, tiles, s);
     }
     if (e != hipSuccess) return hip_fail(e, "gradient GEMM launch");
-    if (pl.fb_splits > 1) {
-      e = sum_parts(p, pl.fb_splits, tc, reinterpret_cast<const float*>(ws + pl.fb_off_ghp), grad_h, t0, s);
+    if (splits > 1) {
+      e = sum_parts(p, splits, tc, reinterpret_cast<const float*>(ws + pl.fb_off_ghp), grad_h, t0, s);
       if (e != hipSuccess) return hip_fail(e, "grad_h sum launch");
     }
   }

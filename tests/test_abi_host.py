@@ -117,6 +117,48 @@ def test_wide_backward_operands_stay_below_4_gib():
     ws_small, _ = B.query_sizes(_fake_problem(M=1, dims=[256], T=T, V=V))
     assert ws_small < T * 256 * 2 * 4
 
+
+def _needed(p):
+    """Bytes the backward and the fused call cannot do without, from their refusals."""
+    fake = 1 << 40
+    g = [fake + (1 << 30) * (i + 1) for i in range(p.M)]
+    out = []
+    for call in (lambda: B.distill_bwd(p, fake, None, None, g, g, fake + (1 << 20), 16, None),
+                 lambda: B.distill_fwd_bwd(p, fake, fake, fake, None, None, None, g, g,
+                                           fake + (1 << 20), 16, None)):
+        with pytest.raises(B.MlsError) as e:
+            call()
+        assert e.value.status == B.MLS_WORKSPACE_TOO_SMALL
+        out.append(int(re.search(r"needs (\d+) workspace", str(e.value)).group(1)))
+    return out
+
+
+@pytest.mark.parametrize("gdt", [B.MLS_F32, B.MLS_BF16])
+@pytest.mark.parametrize("dims,V,chunk", [([2304, 4352], 16000, 0), ([2304, 4352], 8000, 0),
+                                          ([1024, 2048, 3072], 50304, 0), ([512, 1024], 32000, 0),
+                                          ([64], 4096, 0), ([64], 100000, 0), ([200, 408, 1000], 32003, 0),
+                                          ([72, 296], 20011, 8192), ([64, 640], 9000, 1024)])
+def test_a_workspace_for_the_longest_batch_serves_the_shorter_ones(dims, V, chunk, gdt):
+    """The sizes queried, and those a call cannot do without, grow with T: grad_h's K parts
+    (most where tokens are few) neither make a shorter batch need more nor are they
+    needed: a call asks for the slab (and a bf16 grad_h's sums) alone."""
+    M, last = len(dims), (0, 0, 0, 0)
+    Ts = sorted(set(list(range(1, 1400, 37)) + [128, 129, 256, 257, 512, 513] + list(range(1400, 9000, 331))))
+    for T in Ts:
+        p = _fake_problem(M=M, dims=dims, T=T, V=V, vocab_chunk=chunk, grad_h_dtype=gdt)
+        need_bwd, need_fb = _needed(p)
+        now = (B.query_sizes(p)[0], B.query_fwd_bwd_workspace(p), need_bwd, need_fb)
+        assert now[0] >= need_bwd and now[1] >= need_fb
+        assert all(a >= b for a, b in zip(now, last)), (T, now, last)
+        last = now
+        T_pad, Vc = (T + 127) // 128 * 128, (chunk or -(-V // 4) + 255) // 256 * 256
+        slab = M * T_pad * min(Vc, -(-V // 256) * 256) * 2
+        sums = T * sum(dims) * 4 if gdt == B.MLS_BF16 and Vc < V else 0
+        assert need_bwd <= slab + sums + 1024
+        assert now[0] <= max(need_bwd, M * T_pad * (V + 127) // 128 * 32 + M * T * 4,
+                             2 * -(-V // 128) * T * (M * M + 3 * M) * 4 + T * 2 * M * M * 4) + (128 << 20) + 1024
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("M", 0, B.MLS_INVALID_ARG),
     ("M", 9, B.MLS_INVALID_ARG),

@@ -94,3 +94,51 @@ def test_no_sum_without_a_hidden_state_gradient():
                 B.profile_enable(False)
             got[want_h] = gW
         assert all(torch.equal(a, b) for a, b in zip(got[True], got[False]))
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("dims", [(64, 192), (72, 296)])
+def test_any_workspace_from_the_slab_on_is_taken(dims, dt):
+    """A call takes as many parts as its workspace holds: none, some, all of them, and the same ones in
+    any larger workspace; the gradients agree with the oracle and nothing past the workspace is written."""
+    wl = WL.custom(2, 140, dims, 20011, w_std=0.08, seed=66)
+    h, W, y = WL.make_inputs(wl, device=DEV)
+    hn, Wn, yn = to_np(h), to_np(W), y.cpu().numpy()
+    g_ce, g_kl = oracle.coeffs(2, -1, alpha=0.4, tau=1.0)
+    gh, gW = oracle.backward(hn, Wn, yn, g_ce, g_kl)
+    dev = torch.device(DEV)
+    p = D.make_problem(h, W, y, grad_h_dtype=dt)
+    buf = D.Buffers(p, dev)
+    D.forward(p, buf, dev)
+    c = [torch.tensor(v, device=DEV, dtype=torch.float32) for v in (g_ce, g_kl)]
+    part = 140 * sum(dims) * 4
+    for fused in (False, True):
+        size = B.query_fwd_bwd_workspace(p) if fused else buf.ws_bytes
+        with pytest.raises(B.MlsError, match=r"needs \d+ workspace") as e:
+            _call(p, buf, dev, c, h, W, dt, fused, 16)
+        need = int(str(e.value).split("needs ")[1].split()[0])
+        assert need < size
+        seen = {}
+        for nbytes in (need, need + 256, need + 2 * part, need + 3 * part + 256, size, size + 4096):
+            gpu = _call(p, buf, dev, c, h, W, dt, fused, nbytes)
+            check_head_grads(gpu, gh, gW, yn, wl.V, f"{dims} fused={fused} {nbytes} bytes")
+            seen[nbytes] = gpu
+        assert all(np.array_equal(a, b) for a, b in zip(seen[size]["grad_h"], seen[size + 4096]["grad_h"]))
+        assert all(np.array_equal(a, b) for a, b in zip(seen[need]["grad_W"], seen[size]["grad_W"]))
+
+
+def _call(p, buf, dev, c, h, W, dt, fused, nbytes):
+    """Gradients of one backward (or fused call) in a workspace of exactly nbytes, guard bytes behind it."""
+    ws = torch.full((nbytes + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    gh = [torch.full(x.shape, float("nan"), dtype=dt, device=DEV) for x in h]
+    gW = [torch.full(x.shape, float("nan"), device=DEV) for x in W]
+    ptrs = [x.data_ptr() for x in gh], [x.data_ptr() for x in gW]
+    cp = c[0].data_ptr(), c[1].data_ptr()
+    if fused:
+        B.distill_fwd_bwd(p, buf.stats.data_ptr(), buf.ce.data_ptr(), buf.kl.data_ptr(), None, *cp, *ptrs,
+                          ws.data_ptr(), nbytes, D._stream(dev))
+    else:
+        B.distill_bwd(p, buf.stats.data_ptr(), *cp, *ptrs, ws.data_ptr(), nbytes, D._stream(dev))
+    torch.cuda.synchronize()
+    assert torch.all(ws[nbytes:] == 0xA5)
+    return {"grad_h": to_np(gh), "grad_W": to_np(gW)}
