@@ -141,10 +141,16 @@ class _Distill(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g_ce, g_kl, g_ent):
-        saved = ctx.saved_tensors
-        hw = saved[1:]
+        # saved-tensor hooks (offloading to the host, say) hand back other tensors
+        # than forward() saw, which may be gone: the addresses are taken anew
+        labels, *hw = (x.contiguous() for x in ctx.saved_tensors)
         M = ctx.M
         dev = hw[0].device
+        p = B.Problem.from_buffer_copy(ctx.p)
+        p.labels = labels.data_ptr()
+        for i in range(M):
+            p.h[i] = hw[i].data_ptr()
+            p.W[i] = hw[M + i].data_ptr()
         if g_ce is None:
             g_ce = torch.zeros(M, dtype=torch.float32, device=dev)
         if g_kl is None:
@@ -157,7 +163,7 @@ class _Distill(torch.autograd.Function):
         for i in range(M):  # of the inputs' dtype, as forward() set the problem up
             gh.append(torch.empty_like(hw[i]) if need[i] else None)
             gW.append(torch.empty_like(hw[M + i]) if need[M + i] else None)
-        backward(ctx.p, ctx.buf, dev, g_ce, g_kl, gh, gW)
+        backward(p, ctx.buf, dev, g_ce, g_kl, gh, gW)
         return (None, None, *gh, *gW)
 
 

@@ -2,6 +2,8 @@
 identity are taken by value, descriptors are not mixed up between calls, and every
 form of device that names a stream still does."""
 
+from types import SimpleNamespace
+
 import pytest
 import torch
 
@@ -66,3 +68,52 @@ def test_losses_are_outputs_of_their_own():
         assert torch.cuda.memory_allocated() == before
     finally:
         gc.enable()
+
+
+def test_backward_takes_the_addresses_of_the_saved_tensors(monkeypatch):
+    """Saved-tensor hooks may hand the backward other tensors than the forward saw."""
+    old = [torch.zeros(4, 8) for _ in range(4)]
+    p = B.make_problem(2, 4, 4, [8, 8], [x.data_ptr() for x in old[:2]], [x.data_ptr() for x in old[2:]],
+                       torch.zeros(4, dtype=torch.int64).data_ptr(), dtype=B.MLS_F32, tau=1.5)
+    y = torch.ones(4, dtype=torch.int64)
+    new = [torch.ones(8, 4).t() if i == 1 else torch.ones(4, 8) for i in range(4)]  # one of other strides
+    seen = []
+    monkeypatch.setattr(D, "backward", lambda q, buf, dev, gc, gk, gh, gW: seen.append((q, gh, gW)))
+    ctx = SimpleNamespace(saved_tensors=(y, *new), M=2, p=p, buf=None, needs_input_grad=[False, False] + [True] * 4)
+    before = bytes(p)
+    D._Distill.backward(ctx, None, None, None)
+    (q, gh, gW), = seen
+    assert q.labels == y.data_ptr() and q.h[0] == new[0].data_ptr()
+    assert [q.W[0], q.W[1]] == [x.data_ptr() for x in new[2:]]
+    assert q.h[1] not in (old[1].data_ptr(), new[1].data_ptr())  # a contiguous copy
+    assert q.tau == 1.5 and bytes(p) == before
+    assert all(g.is_contiguous() and g.shape == (4, 8) for g in gh + gW)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_gradients_with_saved_tensors_kept_on_the_host(dt):
+    """The hidden states of the forward are given back and written over before the backward."""
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    W = [(torch.randn(700, d, generator=g, device="cuda:0") * 0.1).to(dt) for d in (64, 128)]
+    h0 = [torch.randn(300, d, generator=g, device="cuda:0").to(dt) for d in (64, 128)]
+    y = torch.randint(0, 700, (300,), generator=g, device="cuda:0")
+
+    def grads(offload):
+        leaves = [x.clone().requires_grad_(True) for x in h0 + W]
+        mids = [x * 1.0 for x in leaves]  # not leaves: only the graph keeps them
+        if offload:
+            with torch.autograd.graph.save_on_cpu():
+                ce, kl, _ = D.distill(mids[:2], mids[2:], y, tau=1.5)
+        else:
+            ce, kl, _ = D.distill(mids[:2], mids[2:], y, tau=1.5)
+        loss = (ce + 0.5 * kl).sum()
+        if offload:
+            shapes = [x.shape for x in mids]
+            del mids, ce, kl
+            junk = [torch.full(s, float("nan"), device="cuda:0", dtype=dt) for s in shapes]
+        loss.backward()
+        return [x.grad for x in leaves]
+
+    for a, b in zip(grads(False), grads(True)):
+        assert torch.equal(a, b)
