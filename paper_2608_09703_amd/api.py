@@ -15,6 +15,7 @@ on caller-visible buffers (used by the tests and the benchmark).
 
 from __future__ import annotations
 
+import ctypes
 import functools
 from typing import List, Optional, Sequence
 
@@ -27,6 +28,12 @@ from . import binding as B
 # fields costs about as much as the launch.
 _make_junction = functools.lru_cache(maxsize=256)(B.make_junction)
 _make_sampling = functools.lru_cache(maxsize=256)(B.make_sampling)
+
+
+def _sampling(V, temperature, top_p, greedy) -> B.Sampling:
+    # by value (a tensor hashes by identity), through the fields' own conversion:
+    # what a descriptor refuses (a text, say) is refused
+    return _make_sampling(V, ctypes.c_float(temperature).value, ctypes.c_float(top_p).value, bool(greedy))
 
 
 def _dtype_code(dt: torch.dtype) -> int:
@@ -294,7 +301,7 @@ def sample(logits: torch.Tensor, u: Optional[torch.Tensor], *, temperature: floa
                                params.numel() < rows * B.ROW_PARAMS_BYTES):
         raise ValueError("params must be a contiguous uint8 tensor of rows * ROW_PARAMS_BYTES")
     tok = torch.empty(rows, dtype=torch.int32, device=logits.device)
-    B.sample(_make_sampling(V, float(temperature), float(top_p), bool(greedy)), rows, logits.data_ptr(),
+    B.sample(_sampling(V, temperature, top_p, greedy), rows, logits.data_ptr(),
              u.data_ptr() if u is not None else None, tok.data_ptr(), _stream(logits.device),
              params.data_ptr() if params is not None else None)
     return tok
@@ -335,7 +342,7 @@ def spec_verify(draft_logits: Optional[torch.Tensor], target_logits: torch.Tenso
                                      not draft_params.is_contiguous() or
                                      draft_params.numel() < G * Bt * B.ROW_PARAMS_BYTES):
         raise ValueError("draft_params must be contiguous uint8 of gamma * B records")
-    B.spec_verify(_make_sampling(V, float(temperature), float(top_p), bool(greedy)), Bt, G, ptr(draft_logits),
+    B.spec_verify(_sampling(V, temperature, top_p, greedy), Bt, G, ptr(draft_logits),
                   target_logits.data_ptr(), ptr(draft_tokens), ptr(u_accept), ptr(u_sample),
                   n_acc.data_ptr(), nxt.data_ptr(), ptr(ws), ws_bytes, _stream(dev),
                   draft_params=ptr(draft_params))

@@ -23,6 +23,21 @@ def test_cached_descriptors_carry_their_own_values():
     assert D._make_junction.cache_info().maxsize == D._make_sampling.cache_info().maxsize == 256
 
 
+def test_settings_are_converted_as_the_descriptor_does():
+    import numpy as np
+    t = torch.tensor(0.25)
+    assert D._sampling(1000, t, np.float32(0.5), 1).temperature == 0.25
+    t.fill_(4)
+    assert D._sampling(1000, t, 1, False).temperature == 4.0
+    for bad in ("0.5", b"0.5", None, 1j):
+        with pytest.raises(TypeError):
+            B.make_sampling(1000, bad, 0.9, False)
+        with pytest.raises(TypeError):
+            D._sampling(1000, bad, 0.9, False)
+        with pytest.raises(TypeError):
+            D._sampling(1000, 0.5, bad, False)
+
+
 @pytest.mark.gpu
 def test_settings_as_tensors_are_read_on_every_call():
     g = torch.Generator(device="cuda:0").manual_seed(3)
