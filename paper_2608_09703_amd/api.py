@@ -73,10 +73,13 @@ def make_problem(h: Sequence[torch.Tensor], W: Sequence[torch.Tensor], labels: t
                           grad_h_dtype=_dtype_code(grad_h_dtype))
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # not a public name
+
+
 def _stream(dev) -> int:
     """Handle of the device's current stream (of a tensor's device without building a Stream object)."""
-    if isinstance(dev, torch.device) and dev.index is not None:
-        return torch._C._cuda_getCurrentRawStream(dev.index)
+    if _raw_stream is not None and isinstance(dev, torch.device) and dev.index is not None:
+        return _raw_stream(dev.index)
     return torch.cuda.current_stream(dev).cuda_stream
 
 

@@ -51,8 +51,18 @@ def test_settings_as_tensors_are_read_on_every_call():
     assert torch.equal(second, D.sample(logits, u, temperature=2.0)) and not torch.equal(first, second)
 
 
+def test_stream_without_the_raw_handle(monkeypatch):
+    """A torch build without the raw handle's name: the stream object's."""
+    monkeypatch.setattr(D, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev: SimpleNamespace(cuda_stream=(77, dev)))
+    assert D._stream(torch.device("cuda:1")) == (77, torch.device("cuda:1"))
+
+
 @pytest.mark.gpu
-def test_stream_handles():
+@pytest.mark.parametrize("raw", [True, False], ids=["raw_handle", "stream_object"])
+def test_stream_handles(raw, monkeypatch):
+    if not raw:
+        monkeypatch.setattr(D, "_raw_stream", None)
     side = torch.cuda.Stream()
     for stream in (torch.cuda.current_stream(), side):
         with torch.cuda.stream(stream):
