@@ -74,7 +74,8 @@ def test_ragged_widths_accumulate_and_leave_neighbours_alone():
 @pytest.mark.parametrize("T", [3, 600])
 @pytest.mark.parametrize("d", [8, 72, 120])
 def test_ragged_head_logits(T, d):
-    """Both head tiles (128 and, from four token tiles on, 192 vocabulary rows)."""
+    """One column tile of 32 and several of 128 tokens, 64 vocabulary rows, less than a K-tile and
+    a K-tile with a rest (the larger tiles: test_head_tiles_gpu.py)."""
     g = torch.Generator(device=DEV).manual_seed(T + d)
     o = torch.randn(T, d, generator=g, device=DEV).bfloat16()
     W = torch.randn(391, d, generator=g, device=DEV).bfloat16()
