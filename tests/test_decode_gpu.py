@@ -38,12 +38,13 @@ def _np(x):
 
 HEAD = [
     # T, V, d, dtype
-    (102, 1000, 1024, torch.bfloat16),   # wide bf16 core, one token tile
-    (714, 777, 4352, torch.bfloat16),    # ragged V (scalar stores), several token tiles
-    (600, 5000, 1024, torch.bfloat16),   # many rows: ragged token and vocabulary tiles, float4 stores
-    (512, 3840, 512, torch.bfloat16),    # four token tiles exactly, 192-row vocabulary tiles exactly
-    (5, 49152, 1024, torch.bfloat16),    # full vocabulary, tiny batch
-    (130, 513, 1000, torch.bfloat16),    # general bf16 core (d not a multiple of 64)
+    # tiles: vocabulary rows x token columns
+    (102, 1000, 1024, torch.bfloat16),   # 64 x 128, one token tile
+    (714, 777, 4352, torch.bfloat16),    # 64 x 128, ragged V (scalar stores), several token tiles
+    (600, 5000, 1024, torch.bfloat16),   # 64 x 128, ragged token and vocabulary tiles, float4 stores
+    (512, 3840, 512, torch.bfloat16),    # 64 x 128, four token tiles and 60 vocabulary tiles exactly
+    (5, 49152, 1024, torch.bfloat16),    # 64 x 32, full vocabulary, tiny batch
+    (130, 513, 1000, torch.bfloat16),    # 64 x 128 with a K tail (d not a multiple of 64)
     (33, 300, 100, torch.float32),       # fp32 core
 ]
 
@@ -93,10 +94,9 @@ def test_sample_parity(case):
 
 
 # (logit scale, top_p) at V = 49152, temperature 1: with N(0, scale^2) logits
-# these send rows down each threshold-search path (nucleus sizes from most of
-# the vocabulary down to one token): whole-row search, bound rounds over the
-# row ending in a small or a larger final list, first-list rounds ending in a
-# small or a larger final list.
+# the nucleus sizes go from most of the vocabulary down to one token, and the
+# threshold comes from the run maxima or the radix selection, from lists of every
+# size or from none (test_sample_paths_gpu.py aims at each path by its own rows).
 SCALE_CASES = [(0.01, 0.9), (1.2, 0.5), (2.0, 0.5), (3.0, 0.5), (3.0, 0.7), (4.0, 0.9),
                (4.0, 0.95), (4.0, 0.97), (5.0, 0.99), (8.0, 0.99)]
 

@@ -1,7 +1,7 @@
 """GPU parity of the cross-model diagnostics (pairwise KL at temperature 1 and
 top-1 agreement, paper section 3) against the float64 oracle.
 
-Small cases run the whole oracle on every path (wide bf16, general bf16,
+Small cases run the whole oracle on every path (bf16, bf16 with K tails,
 float32; the 128x128 tile for M <= 2 and the 128x64 tile for M = 3, 4) with
 ragged token and vocabulary tails. Argmax is an integer decided by floating
 point: a GPU index is accepted when its float64 logit is within the fp32
@@ -97,8 +97,8 @@ SMALL = [
     ("m4_random", WL.custom(4, 200, (64, 64, 128, 256), 777, w_std=0.05, ignore_frac=0.2, seed=23),
      False),
     ("m1", WL.custom(1, 130, (96,), 300, w_std=0.1, seed=24), False),
-    ("m2_general_bf16", WL.custom(2, 140, (72, 136), 600, w_std=0.1, w_scale=2.0, seed=25), True),
-    ("m3_general_bf16", WL.custom(3, 140, (40, 72, 136), 650, w_std=0.1, w_scale=2.0, seed=26), True),
+    ("m2_ragged_bf16", WL.custom(2, 140, (72, 136), 600, w_std=0.1, w_scale=2.0, seed=25), True),
+    ("m3_ragged_bf16", WL.custom(3, 140, (40, 72, 136), 650, w_std=0.1, w_scale=2.0, seed=26), True),
     ("m2_f32", WL.WORKLOADS["c1_small_f32"], False),
     ("m3_f32_ragged", WL.custom(3, 150, (32, 36, 100), 555, dtype="f32", w_std=0.1, w_scale=2.0,
                                 ignore_frac=0.1, seed=27), True),
@@ -115,7 +115,7 @@ SMALL = [
                                     ignore_frac=0.1, seed=37), True),
     ("m8_nested_subsets", WL.custom(8, 200, (64, 64, 128, 128, 192, 192, 256, 320), 1100,
                                     w_std=0.1, w_scale=3.0, ignore_frac=0.1, seed=38), True),
-    ("m6_general_bf16", WL.custom(6, 140, (40, 72, 72, 136, 136, 200), 650, w_std=0.1, w_scale=2.0,
+    ("m6_ragged_bf16", WL.custom(6, 140, (40, 72, 72, 136, 136, 200), 650, w_std=0.1, w_scale=2.0,
                                   seed=39), True),
     ("m7_f32", WL.custom(7, 130, (32, 36, 36, 64, 64, 100, 100), 555, dtype="f32", w_std=0.1,
                          w_scale=2.0, ignore_frac=0.1, seed=40), False),

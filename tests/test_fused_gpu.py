@@ -131,9 +131,9 @@ def test_fused_accumulate_flags_and_skipped_gradients():
                                                  (300, (72, 136), "bf16", 0),
                                                  (300, (32, 36), "f32", 0),
                                                  (300, (64, 128), "bf16", B.MLS_FWD_BWD_RECOMPUTE)],
-                         ids=["one_tile", "general_widths", "f32", "recompute_flag"])
+                         ids=["one_tile", "ragged_widths", "f32", "recompute_flag"])
 def test_fused_entry_point_falls_back_to_recompute(T, dims, dtype, flags):
-    """One token tile, widths off the wide path, fp32 inputs or the recompute flag:
+    """One token tile, widths that are not multiples of 64, fp32 inputs or the recompute flag:
     the call runs the forward and the recomputing backward, with the same results
     as the two separate calls."""
     wl = WL.custom(2, T, dims, 900, dtype=dtype, tau=1.2, w_std=0.1, ignore_frac=0.1, seed=33)

@@ -288,8 +288,8 @@ def test_full_size_backward_is_bitwise_repeatable(name):
 @pytest.mark.parametrize("dtype,chunk", [("bf16", 512), ("f32", 256)])
 def test_accumulate_flags_and_skipped_gradients(dtype, chunk):
     """MLS_ACCUMULATE_GRAD_W / _H add to the caller's gradients instead of
-    overwriting them (over several vocabulary chunks), on the wide bf16 and
-    the general fp32 paths; NULL gradient pointers skip those outputs and the
+    overwriting them (over several vocabulary chunks), on the bf16 and
+    the fp32 paths; NULL gradient pointers skip those outputs and the
     others are still right."""
     from paper_2608_09703_amd import api as D
     from paper_2608_09703_amd import binding as B
@@ -327,7 +327,7 @@ def test_accumulate_flags_and_skipped_gradients(dtype, chunk):
                                               ((64, 128, 192), "bf16", 0),
                                               ((72, 136, 200), "bf16", 256),
                                               ((32, 36, 100), "f32", 256)],
-                         ids=["wide_chunks", "wide_default", "general_bf16", "general_f32"])
+                         ids=["wide_chunks", "wide_default", "ragged_bf16", "f32"])
 def test_bf16_grad_h_is_the_rounded_fp32_gradient(dims, dtype, chunk):
     """grad_h_dtype = bf16: the fp32 sums (kept in fp32 across vocabulary chunks) rounded
     once, so the result equals the fp32 output rounded to bf16, bit for bit; with
