@@ -154,11 +154,14 @@ typedef struct mls_problem {
  *                    and room for fp32 sums of grad_h taken in parts; the
  *                    diagnostics' two records of (M*M + 3M) floats per token
  *                    and 128-row vocabulary tile. The room for the parts (at
- *                    most 128 MiB) is reported such that a size queried for
- *                    some T suffices for every smaller T of the same problem.
- *                    It is not required: each call accepts any workspace that
- *                    holds the rest, and takes as many parts as fit, which
- *                    changes its speed and the order of grad_h's fp32 sums.
+ *                    most 128 MiB) is reported such that it makes no size
+ *                    queried for some T too small for a smaller T of the same
+ *                    problem. (The slab can: where one chunk's slabs would pass
+ *                    4 GiB, chunks become narrower as T grows, and the reported
+ *                    size may fall.) The room is not required: each call accepts
+ *                    any workspace that holds the rest, and takes as many parts
+ *                    as fit, which changes its speed and the order of grad_h's
+ *                    fp32 sums.
  *   stats_bytes      per-row statistics the forward writes and the backward
  *                    reads. Layout (all little-endian, offsets in elements of
  *                    float32 from the start):
