@@ -184,8 +184,8 @@ int64_t max_parts(int64_t vrows) {
 // and 4,815-4,828 us (T = 6,990, widths 320 / 384 / 704, V = 64,512). Forward +
 // backward in one call, before there were parts (and with a main loop 3 % slower)
 // and with them: T = 512, widths 1,024 / 2,048 / 3,072, V = 50,304: 3,273 ->
-// 1,829 us; T = 1,024, widths 512 / 1,024, V = 32,000: 1,394 -> 483 us. With 4,096 tokens of the headline shape one part
-// remains the shortest.
+// 1,829 us; T = 1,024, widths 512 / 1,024, V = 32,000: 1,394 -> 483 us. With
+// 4,096 tokens of the headline shape one part remains the shortest.
 void grad_h_parts(const mls_problem* p, int64_t rows, int64_t vrows, size_t room, int* splits,
                   int64_t* ksplit) {
   constexpr int64_t kTileCost = 6;       // K-tiles
@@ -255,10 +255,11 @@ int64_t chunk_rows(const mls_problem* p, const Plan& pl, int64_t T_pad) {
   if (p->vocab_chunk > 0) {
     vc = round_up(p->vocab_chunk, 256);
   } else {
-    // At least kMinChunks balanced chunks, more when the slabs of one chunk
-    // would exceed kSlabTargetBytes (the wide path keeps one slab layout, the
-    // general path two), so the logit-gradient slab never spans the whole
-    // vocabulary (V > 256).
+    // At least kMinChunks balanced chunks, so that the logit-gradient slab never
+    // spans the whole vocabulary (V > 256), and more where two slab layouts (one
+    // on the wide path at multiples of 64) would exceed kSlabTargetBytes. Only the
+    // general path keeps both; fp32 and the other bf16 widths keep one and have
+    // the chunks of two all the same.
     const int64_t per_row = (pl.wide_bwd && !pl.ktail ? 1ll : 2ll) * pl.M * T_pad * pl.es;
     const int64_t fit = std::max<int64_t>(256, kSlabTargetBytes / per_row / 256 * 256);
     const int64_t n = std::max<int64_t>(kMinChunks, (p->V + fit - 1) / fit);
@@ -789,27 +790,27 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
 
     // general path: W_i[chunk]^T [d_i, Vc] for the grad_h products
     if (!stored) {
-    TransposeArgs ta;
-    memset(&ta, 0, sizeof(ta));
-    int64_t maxc = 0;
-    for (int i = 0; i < pl.M; ++i) {
-      if (!grad_h[i]) continue;
-      TransposeJob& j = ta.j[ta.njobs++];
-      j.src = p->W[i];
-      j.dst = WT + (size_t)doff[i] * pl.Vc * pl.es;
-      j.ld_src = p->d[i];
-      j.ld_dst = pl.Vc;
-      j.r0 = v0;
-      j.src_rows = pl.V;
-      j.out_rows = pl.Vc;
-      j.cols = p->d[i];
-      maxc = std::max(maxc, p->d[i]);
-    }
-    {
-      ProfScope ps("transpose_W", s);
-      e = launch_transpose(ta, pl.Vc, maxc, s);
-    }
-    if (e != hipSuccess) return hip_fail(e, "transpose launch");
+      TransposeArgs ta;
+      memset(&ta, 0, sizeof(ta));
+      int64_t maxc = 0;
+      for (int i = 0; i < pl.M; ++i) {
+        if (!grad_h[i]) continue;
+        TransposeJob& j = ta.j[ta.njobs++];
+        j.src = p->W[i];
+        j.dst = WT + (size_t)doff[i] * pl.Vc * pl.es;
+        j.ld_src = p->d[i];
+        j.ld_dst = pl.Vc;
+        j.r0 = v0;
+        j.src_rows = pl.V;
+        j.out_rows = pl.Vc;
+        j.cols = p->d[i];
+        maxc = std::max(maxc, p->d[i]);
+      }
+      {
+        ProfScope ps("transpose_W", s);
+        e = launch_transpose(ta, pl.Vc, maxc, s);
+      }
+      if (e != hipSuccess) return hip_fail(e, "transpose launch");
     }
 
     a.v0 = v0;
@@ -818,7 +819,7 @@ mls_status mls_distill_bwd(const mls_problem* p, const void* stats, const float*
       // K-tile holding its last row (grad_h) or for output rows it does not
       // store (grad_W), the fp32 one only in whole 16-byte chunks, so the
       // vocabulary tiles past the chunk end are skipped.
-      if (pl.f32 || fbm % gemm_wide_k_tile() == 0) a.n_vt = (int)((vrows + fbm - 1) / fbm);
+      a.n_vt = (int)((vrows + fbm - 1) / fbm);
     }
     {
       ProfScope ps("fused_bwd", s);

@@ -445,8 +445,8 @@ __device__ __forceinline__ int run_index(const RowShared& sh, int q) {
 
 // Position in the list of the first entry (index order) whose cumulative
 // weight exceeds `target`; the last positive entry when rounding leaves the
-// target at or above the sum; 0 when every weight is 0 (a kept set never is
-// empty: the largest weight is 1 and theta <= 1).
+// target at or above the sum; 0 when every weight is 0, which the callers rule
+// out (a row that keeps no token has no list to draw from).
 template <int RUN>
 __device__ __forceinline__ int run_draw(const float (&kw)[RUN], float target) {
   const int lane = threadIdx.x & 63;
@@ -1044,31 +1044,31 @@ __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
       next = n <= kSmallCand ? list_residual_draw<4>(sh, n, dp, drow, dq, it, a.u_sample[b])
                              : list_residual_draw<kRunMax>(sh, n, dp, drow, dq, it, a.u_sample[b]);
     } else {
-    auto res = [&](int i) {
-      const int v = elem_v<EPT>(i);
-      if (v >= V) return 0.f;
-      return fmaxf(prob_at(trow, v, it, dp) - prob_at(drow, v, it, dq), 0.f);
-    };
-    float rs = 0.f;
+      auto res = [&](int i) {
+        const int v = elem_v<EPT>(i);
+        if (v >= V) return 0.f;
+        return fmaxf(prob_at(trow, v, it, dp) - prob_at(drow, v, it, dq), 0.f);
+      };
+      float rs = 0.f;
 #pragma unroll 4
-    for (int i = 0; i < EPT; ++i) rs += res(i);
-    const float tot = block_sum(rs, sh);
-    if (tot > 0.f) {
-      int v = index_order_draw<EPT>(res, a.u_sample[b] * tot, sh);
-      if (v < 0) {
-        int last = -1;
-        for (int i = 0; i < EPT; ++i)
-          if (res(i) > 0.f) last = elem_v<EPT>(i);
-        float lv = (float)last;
-        block_argmax(lv, last, sh);
-        v = last;
+      for (int i = 0; i < EPT; ++i) rs += res(i);
+      const float tot = block_sum(rs, sh);
+      if (tot > 0.f) {
+        int v = index_order_draw<EPT>(res, a.u_sample[b] * tot, sh);
+        if (v < 0) {
+          int last = -1;
+          for (int i = 0; i < EPT; ++i)
+            if (res(i) > 0.f) last = elem_v<EPT>(i);
+          float lv = (float)last;
+          block_argmax(lv, last, sh);
+          v = last;
+        }
+        next = v;
+      } else {
+        // no residual mass: the rejected token was impossible under both
+        // distributions and they coincide, so the draw is from the verifier's
+        next = draw_kept<EPT>(trow, V, it, dp, a.u_sample[b], sh);
       }
-      next = v;
-    } else {
-      // no residual mass: the rejected token was impossible under both
-      // distributions and they coincide, so the draw is from the verifier's
-      next = draw_kept<EPT>(trow, V, it, dp, a.u_sample[b], sh);
-    }
     }
   }
   if (k == G) {  // every draft kept: one more token from the verifier
@@ -1097,8 +1097,8 @@ __global__ __launch_bounds__(kRowThreads) void verify_kernel(VerifyArgs a) {
 using HeadWide = WideMma<128, 128, 2, 2, 2>;
 // 192 vocabulary rows: 80 KB of stages, two blocks fill a CU's LDS
 using HeadWide192 = WideMma<192, 128, 2, 2, 2>;
-// few rows: a quarter (half) of the token columns, so that more K-tiles of the
-// head fit in flight: 36 (32) KB per block, three blocks per CU
+// few rows: a quarter (half) of the token columns, so that three (two) K-tiles
+// of the head are in flight ahead: 48 KB of stages, three blocks per CU
 using HeadFew = WideMma<64, 32, 2, 1, 4>;
 using HeadSome = WideMma<64, 64, 2, 2, 3>;
 // 128 columns, vocabularies too small for a 128-row block per CU
@@ -1115,8 +1115,8 @@ using HeadGenF32 = TileMma<F32, 128, 128, 2, 2>;
 
 // Tile of the head product (vocabulary rows x token columns).
 // - At most 64 rows of hidden states: bound by the head's bytes and by how many
-//   of them are in flight, so 64 vocabulary rows and 32 or 64 columns, whose
-//   stages leave room for three K-tiles ahead in three blocks per CU. One row at
+//   of them are in flight, so 64 vocabulary rows and 32 or 64 columns, with
+//   three or two K-tiles ahead in each of three blocks per CU. One row at
 //   width 4,352, V = 49,152: 84 -> 74 us (5.8 TB/s); 16 rows at width 2,048, V =
 //   16,000: 31 -> 16 us; 64 rows at width 4,352: 94 -> 91 us.
 // - 128 columns otherwise. Where 128-row tiles would not give every CU a block,

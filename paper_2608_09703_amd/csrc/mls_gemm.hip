@@ -222,6 +222,8 @@ constexpr int kWideBM = 256;
 constexpr int kWideBN = 256;
 using WideGemmH = WideMma<kWideBM, kWideBN, 2, 4, 5, 64, kLayoutKC, kLayoutMC>;
 using WideGemmW = WideMma<kWideBM, kWideBN, 2, 4, 5, 64, kLayoutMC, kLayoutMC>;
+static_assert(kFusedBM % WideGemmH::BK == 0,
+              "the K-tile holding a chunk's last row lies in a tile that the logit-gradient kernel writes");
 
 // Loads and stores of one wave's part of an output tile through buffer
 // descriptors over the tile's existing rows (rows past them read as 0 and are
