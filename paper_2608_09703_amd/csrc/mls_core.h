@@ -428,8 +428,8 @@ struct WideMma {
   // and STAGES - 1 K-tiles stay in flight. Against two stages of 64-wide K, whose
   // first fragments are read after the barrier, the 256 x 256 gradient GEMM with
   // five stages of 32-wide K takes 4.31 instead of 4.44 ms per headline step, timed
-  // in turn (1.18 PFLOP/s; 4.22 to 4.42 ms by box and under a profiler), and 4
-  // stages the same. What was left on the box where it took 4.22: without its
+  // in turn (1.18 PFLOP/s; 4.2 to 4.5 ms by card and under a profiler), and 4
+  // stages the same. What was left on the card where it took 4.22: without its
   // loads the loop took 3.5 ms, without its fragment reads no less, and with every
   // tile on the same panels (all loads hit L2) 4.02, at a clock near 1.8 GHz.
   template <class Init>
